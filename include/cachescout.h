@@ -273,6 +273,49 @@ int cs_paged_decode_attn(const void *q, const void *k_pool, const void *v_pool,
                          int32_t block_size, float scale, void *out, cs_stream_t stream);
 
 /*
+ * The same decode with a caller workspace, which lets any batch fill the
+ * device (Sec. 5's per-turn latency, as cs_paged_decode_attn).
+ *
+ * cs_paged_decode_attn gives every (sequence, KV head) one work-group.  This
+ * call counts the batch's keys in units of 32 and deals them to a few one-wave
+ * work-groups per compute unit, in equal contiguous ranges, or, where two
+ * sequences hold the same pool block at index 31 (a shared anchor), in pieces
+ * cut at the same positions of every sequence.  A sequence cut over several
+ * ranges leaves fp32 partial results (O relative to its running maximum m,
+ * m, and the probability sum l) in the workspace, which a second kernel
+ * combines with log-sum-exp weights into the bf16 output.  The plan is made
+ * on the device from seq_lens, so a loose max_seq_len costs nothing.  The
+ * result equals cs_paged_decode_attn's up to rounding order, and is the same
+ * from run to run.  Batches above 1024, calls with max_seq_len up to 128, and at
+ * head_dim 64 up to 512 while batch * num_kv_heads <= compute units, ignore the
+ * workspace and run exactly as cs_paged_decode_attn; so does a call whose out
+ * is not 16-byte aligned.
+ *
+ * Arguments as in cs_paged_decode_attn, plus
+ *   workspace        device, 16-byte aligned, caller-owned scratch of at least
+ *                    cs_paged_decode_workspace_bytes(batch, max_seq_len,
+ *                    num_q_heads, num_kv_heads, head_dim, 0) bytes (may be
+ *                    NULL when that is 0); its contents are undefined after
+ *                    the call; calls that share a workspace must be ordered
+ *                    on one stream.
+ *   workspace_bytes  its size; smaller than required -> CS_ERR_INVALID_ARG.
+ */
+int cs_paged_decode_attn_ws(const void *q, const void *k_pool, const void *v_pool,
+                            const int32_t *block_tables, const int32_t *seq_lens, int32_t batch,
+                            int32_t max_seq_len, int32_t max_blocks_per_seq, int32_t num_blocks,
+                            int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                            int32_t block_size, float scale, void *workspace,
+                            int64_t workspace_bytes, void *out, cs_stream_t stream);
+
+/* Workspace bytes cs_paged_decode_attn_ws needs: (2 * max(1, 8 * CUs /
+ * num_kv_heads) + batch) * num_q_heads * (head_dim + 2) * 4 + 8, or 0 when the
+ * call ignores the workspace.  num_cus: compute units to size for, 0 = the
+ * current device's (-1 if there is none).  -1 for a negative size, bad head
+ * counts or a head_dim other than 64 or 128. */
+int64_t cs_paged_decode_workspace_bytes(int32_t batch, int32_t max_seq_len, int32_t num_q_heads,
+                                        int32_t num_kv_heads, int32_t head_dim, int32_t num_cus);
+
+/*
  * Cascade (shared-prefix) decode: the same result as cs_paged_decode_attn,
  * computed so that a prefix shared by a group of sequences is read once.
  *

@@ -278,6 +278,77 @@ int validate_decode(const void* q, const void* k_pool, const void* v_pool,
 
 namespace {
 
+// Workspace bytes of a decode launch in ranges: per slot, an fp32 O row and
+// (m, l) for every query head, and the launch's plan; 0 without ranges.
+int64_t decode_range_bytes(const cs::DecodeGeometry& geo, int32_t num_q_heads, int32_t head_dim) {
+  if (geo.ranges == 0) return 0;
+  return (int64_t)geo.slots * num_q_heads * (head_dim + 2) * (int64_t)sizeof(float) +
+         (int64_t)sizeof(int2);
+}
+
+// cs_paged_decode_attn, and with a workspace (has_ws) the variant whose
+// launches deal their keys out in ranges
+int paged_decode(const void* q, const void* k_pool, const void* v_pool,
+                 const int32_t* block_tables, const int32_t* seq_lens, int32_t batch,
+                 int32_t max_seq_len, int32_t max_blocks_per_seq, int32_t num_blocks,
+                 int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t block_size,
+                 float scale, bool has_ws, void* workspace, int64_t workspace_bytes, void* out,
+                 cs_stream_t stream) {
+  bool noop;
+  int st0 = validate_decode(q, k_pool, v_pool, block_tables, seq_lens, batch, max_seq_len,
+                            max_blocks_per_seq, num_blocks, num_q_heads, num_kv_heads, head_dim,
+                            block_size, scale, out, &noop);
+  if (st0 != CS_OK) return st0;
+  if (has_ws && workspace_bytes < 0) return fail(CS_ERR_INVALID_ARG, "negative workspace_bytes");
+  if (noop) return ok();
+  cs::DecodeGeometry geo = {};
+  if (has_ws) {
+    int cus = 0;
+    hipError_t ecu = cs::current_device_cus(&cus);
+    if (ecu != hipSuccess) return hip_fail(ecu, "compute-unit count of the current device");
+    geo = cs::decode_geometry(batch, max_seq_len, num_kv_heads, head_dim, cus);
+    const int64_t need = decode_range_bytes(geo, num_q_heads, head_dim);
+    if (need > 0) {
+      if (!workspace || !aligned16(workspace))
+        return fail(CS_ERR_INVALID_ARG, "workspace must be a 16-byte aligned device buffer");
+      if (workspace_bytes < need)
+        return fail(CS_ERR_INVALID_ARG, "workspace_bytes %lld < %lld required",
+                    (long long)workspace_bytes, (long long)need);
+      if (!aligned16(out)) geo = {};   // the range kernels store eight bytes at a time
+    }
+  }
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (debug_checks_enabled()) {
+    int st = debug_check_decode(block_tables, seq_lens, batch, max_seq_len, max_blocks_per_seq,
+                                num_blocks, s);
+    if (st != CS_OK) return st;
+  }
+  cs::DecodeLaunch a;
+  a.q = static_cast<const uint16_t*>(q);
+  a.k_pool = static_cast<const uint16_t*>(k_pool);
+  a.v_pool = static_cast<const uint16_t*>(v_pool);
+  a.block_tables = block_tables;
+  a.seq_lens = seq_lens;
+  a.out = static_cast<uint16_t*>(out);
+  a.batch = batch;
+  a.max_blocks_per_seq = max_blocks_per_seq;
+  a.num_q_heads = num_q_heads;
+  a.num_kv_heads = num_kv_heads;
+  a.head_dim = head_dim;
+  a.scale = scale;
+  a.ranges = geo.ranges;
+  a.aligned_ranges = geo.aligned_ranges;
+  a.slots = geo.slots;
+  a.workspace = geo.ranges > 0 ? workspace : nullptr;
+  hipError_t e = cs::launch_paged_decode_attn(a, s);
+  if (e != hipSuccess) return hip_fail(e, "paged_decode_attn launch");
+  return ok();
+}
+
+}  // namespace
+
+namespace {
+
 // Workspace bytes of a launch with key parts: per part, an fp32 O row and
 // (m, l) for every (token, query head); 0 without parts.
 int64_t key_part_bytes(const cs::AttnGeometry& geo, int32_t total_q, int32_t num_q_heads,
@@ -616,34 +687,32 @@ int cs_paged_decode_attn(const void* q, const void* k_pool, const void* v_pool,
                          int32_t max_seq_len, int32_t max_blocks_per_seq, int32_t num_blocks,
                          int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
                          int32_t block_size, float scale, void* out, cs_stream_t stream) {
-  bool noop;
-  int st0 = validate_decode(q, k_pool, v_pool, block_tables, seq_lens, batch, max_seq_len,
-                            max_blocks_per_seq, num_blocks, num_q_heads, num_kv_heads, head_dim,
-                            block_size, scale, out, &noop);
-  if (st0 != CS_OK) return st0;
-  if (noop) return ok();
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (debug_checks_enabled()) {
-    int st = debug_check_decode(block_tables, seq_lens, batch, max_seq_len, max_blocks_per_seq,
-                                num_blocks, s);
-    if (st != CS_OK) return st;
-  }
-  cs::DecodeLaunch a;
-  a.q = static_cast<const uint16_t*>(q);
-  a.k_pool = static_cast<const uint16_t*>(k_pool);
-  a.v_pool = static_cast<const uint16_t*>(v_pool);
-  a.block_tables = block_tables;
-  a.seq_lens = seq_lens;
-  a.out = static_cast<uint16_t*>(out);
-  a.batch = batch;
-  a.max_blocks_per_seq = max_blocks_per_seq;
-  a.num_q_heads = num_q_heads;
-  a.num_kv_heads = num_kv_heads;
-  a.head_dim = head_dim;
-  a.scale = scale;
-  hipError_t e = cs::launch_paged_decode_attn(a, s);
-  if (e != hipSuccess) return hip_fail(e, "paged_decode_attn launch");
-  return ok();
+  return paged_decode(q, k_pool, v_pool, block_tables, seq_lens, batch, max_seq_len,
+                      max_blocks_per_seq, num_blocks, num_q_heads, num_kv_heads, head_dim,
+                      block_size, scale, false, nullptr, 0, out, stream);
+}
+
+int cs_paged_decode_attn_ws(const void* q, const void* k_pool, const void* v_pool,
+                            const int32_t* block_tables, const int32_t* seq_lens, int32_t batch,
+                            int32_t max_seq_len, int32_t max_blocks_per_seq, int32_t num_blocks,
+                            int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim,
+                            int32_t block_size, float scale, void* workspace,
+                            int64_t workspace_bytes, void* out, cs_stream_t stream) {
+  return paged_decode(q, k_pool, v_pool, block_tables, seq_lens, batch, max_seq_len,
+                      max_blocks_per_seq, num_blocks, num_q_heads, num_kv_heads, head_dim,
+                      block_size, scale, true, workspace, workspace_bytes, out, stream);
+}
+
+int64_t cs_paged_decode_workspace_bytes(int32_t batch, int32_t max_seq_len, int32_t num_q_heads,
+                                        int32_t num_kv_heads, int32_t head_dim, int32_t num_cus) {
+  if (batch < 0 || max_seq_len < 0 || num_cus < 0 || num_q_heads <= 0 || num_kv_heads <= 0 ||
+      num_q_heads % num_kv_heads != 0 || (head_dim != 64 && head_dim != 128))
+    return -1;
+  if (batch == 0) return 0;
+  int cus = num_cus;
+  if (cus == 0 && cs::current_device_cus(&cus) != hipSuccess) return -1;
+  return decode_range_bytes(cs::decode_geometry(batch, max_seq_len, num_kv_heads, head_dim, cus), num_q_heads,
+                            head_dim);
 }
 
 int64_t cs_cascade_decode_workspace_bytes(int32_t batch, int32_t num_q_heads, int32_t head_dim,

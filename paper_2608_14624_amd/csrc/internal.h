@@ -116,8 +116,25 @@ struct DecodeLaunch {
   int num_kv_heads;
   int head_dim;
   float scale;
+  int ranges;               // decode_geometry's (0: one work-group per sequence and KV head)
+  int aligned_ranges;
+  int slots;
+  void* workspace;          // decode_workspace_bytes of scratch (ranges > 0 only)
 };
 
+// A decode launch with a workspace deals the batch's keys to one-wave
+// work-groups, `ranges` per KV head (`aligned_ranges` where sequences share
+// blocks), which leave partial results in `slots` workspace slots per KV head.
+// All 0: one work-group per (sequence, KV head) instead, no workspace.
+struct DecodeGeometry {
+  int ranges;
+  int aligned_ranges;
+  int slots;
+};
+// largest batch for ranges (every wave reads all lengths to make its plan)
+constexpr int kRangeMaxBatch = 1024;
+
+DecodeGeometry decode_geometry(int batch, int max_seq_len, int num_kv_heads, int head_dim, int cus);
 hipError_t launch_paged_decode_attn(const DecodeLaunch& a, hipStream_t stream);
 
 // Cascade decode: the shared prefix of each group of sequences is attended

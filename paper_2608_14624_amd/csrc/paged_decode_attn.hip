@@ -37,6 +37,9 @@
 
 #include <math.h>
 
+#include <algorithm>
+#include <type_traits>
+
 namespace cs {
 namespace {
 
@@ -72,6 +75,12 @@ struct DecParams {
   int num_kv_heads;
   int group;
   float scale_log2;
+  // decode in ranges (decode_ranges_kernel): work-groups per KV head, partials
+  // per KV head in ws_o / ws_ml, and the plan ({aligned, units per piece})
+  int ranges;
+  int aligned_ranges;
+  int slots;
+  int2* plan;
   // cascade mode only
   const int32_t* cu_groups;     // [num_groups + 1], cu_groups[0] = 0, last = batch
   const int32_t* shared_lens;   // [num_groups]
@@ -350,6 +359,506 @@ __global__ __launch_bounds__(64 * (kCascade ? kCascadeWaves : kDecodeWaves)) voi
   }
 }
 
+// ---- decode in ranges ----------------------------------------------------
+//
+// One wave per work-group, a few per CU, p.ranges of them per KV head whatever
+// the batch holds.  The sequences' keys are counted in units of 32 (one chunk),
+// and every wave works the plan out itself from the lengths (wave-wide scans),
+// so the host needs no lengths and no tight bound of them.
+//   * Nothing shared: the sequences' units are laid end to end in batch order
+//     and dealt in equal contiguous ranges of ceil(total / ranges) units.
+//   * Sequences that share a prefix (the same pool block at index
+//     kProbeBlock of two block tables): every sequence is cut at the same
+//     positions, multiples of ceil(total / (kAlignedPieces ranges)) units, and
+//     the waves take the first pieces of all sequences, then the second ones, ...,
+//     so that sequences with the same blocks read them at about the same time
+//     and most find them in L2.
+// A piece of a sequence that is not the whole of it leaves a partial result (O
+// relative to its running max m, the max m and the sum l) in a slot of the
+// workspace, and decode_ranges_merge_kernel combines a sequence's pieces.  The
+// slot of a contiguous piece is r + w (sequence r, range w: both grow from piece
+// to piece, so slots are unique), of an aligned piece its index among all.
+//
+// What bounds it is HBM, and how it is asked: 4 KiB (block, head) tiles at
+// scattered places.  More requests in flight than the memory needs make some
+// waves starve (first loads served after 60 us of a 90 us launch) while the
+// slowest range sets the time, and ordinary loads wash the whole stream through
+// the last-level cache.  128 sequences of 6000-9000 keys, 32 / 8 heads of 128:
+// twelve waves per CU as work-groups of four 659 us, with non-temporal loads
+// 612, four single-wave work-groups per CU and non-temporal loads 574, three
+// 571 (6.7 TB/s; one 12-wave work-group per sequence and KV head: 642).  Three
+// per CU at head_dim 128 (two: 1% slower, five: 6%), four at 64, where a wave's
+// chunk is half the bytes (three: 5% slower).  K and V both non-temporal is up
+// to 4% faster than V alone, but 17% slower where the pools were written just
+// before (4 GB of them: 875 us against 749; ordinary loads 797).  Sequences that
+// share want ordinary loads and more waves: 128 sequences of 8 agents 317 us
+// with eight per CU and two pieces per range, 355 with four and four, 486 as
+// contiguous non-temporal ranges (one 12-wave work-group per sequence and KV
+// head: 330).
+constexpr int kRangeGroupsPerCu128 = 3;
+constexpr int kRangeGroupsPerCu64 = 4;
+constexpr int kAlignedGroupsPerCu = 8;
+constexpr int kAlignedPieces = 2;
+constexpr int kUnitKeys = kChunk;
+constexpr int kUnitBlocks = kUnitKeys / kBlock;
+constexpr int kProbeBlock = 31;
+constexpr int kProbeTable = 2 * kRangeMaxBatch;
+// word 3 of a raw buffer descriptor (32-bit data format, no swizzle), and the
+// cache policy bit of a non-temporal buffer load
+constexpr int kRawBufferWord3 = 0x00020000;
+constexpr int kNonTemporal = 2;
+
+__device__ __forceinline__ int units_of(int len) { return (max(len, 0) + kUnitKeys - 1) / kUnitKeys; }
+
+// inclusive prefix sum over the 64 lanes (DPP: shifts within rows of 16, then
+// row 15 and row 31 broadcasts; lanes without a source add 0)
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31
+  return x;
+}
+__device__ __forceinline__ int wave_total(int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
+
+__device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// units of sequence s (a lane's), 0 past the batch
+__device__ __forceinline__ int units_at(const DecParams& p, int s) {
+  return s < p.batch ? units_of(p.seq_lens[s]) : 0;
+}
+
+// whether two sequences hold the same pool block at index kProbeBlock: a hash
+// table of the blocks in LDS (one wave; at most half full)
+__device__ __forceinline__ bool shares_blocks(const DecParams& p, int lane, int* table) {
+  for (int i = lane; i < kProbeTable; i += 64) table[i] = -1;
+  __syncthreads();
+  bool dup = false;
+  for (int s = lane; s < p.batch; s += 64) {
+    if (p.seq_lens[s] <= kProbeBlock * kBlock) continue;
+    const int id = p.block_tables[(size_t)s * p.max_blocks_per_seq + kProbeBlock];
+    unsigned h = ((unsigned)id * 2654435761u) >> 16;
+    for (int tries = 0; tries < kProbeTable; ++tries) {
+      h %= kProbeTable;
+      const int old = atomicCAS(&table[h], -1, id);
+      if (old == -1) break;
+      if (old == id) {
+        dup = true;
+        break;
+      }
+      ++h;
+    }
+  }
+  __syncthreads();
+  return __builtin_amdgcn_ballot_w64(dup) != 0;
+}
+
+// A position in a wave's list of pieces.
+struct RangeCursor {
+  int r;          // sequence
+  int len;        // its keys
+  int x, xe;      // unit within the sequence, end of the piece
+  int slot;       // where the piece's partial goes, -1: the piece is the whole sequence
+  bool valid;
+};
+
+template <int D>
+__global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
+  constexpr int vStride = DecLds<D, 1>::vStride;
+  constexpr int DC = D / 32;
+  constexpr int DT = D / 16;
+  constexpr int kRowChunks = D / 8;
+  constexpr int kVLoads = kChunk * kRowChunks / 64;
+  constexpr int kTileBytes = kBlock * D * 2;           // one (block, head)
+  __shared__ union {
+    uint16_t v[kChunk * vStride];
+    int probe[kProbeTable];
+  } sm;
+
+  const int lane = threadIdx.x;
+  const int j = lane & 15;
+  const int qd = lane >> 4;
+  const int g = blockIdx.x % p.num_kv_heads;
+  const int w = blockIdx.x / p.num_kv_heads;
+  typedef const __attribute__((address_space(4))) int32_t* ScalarInts;
+  const ScalarInts lens_c = (ScalarInts)p.seq_lens;
+
+  // ---- the plan
+  int total = 0;
+  for (int s = 0; s < p.batch; s += 64) total += wave_total(units_at(p, s + lane));
+  const bool aligned = p.batch > 1 && shares_blocks(p, lane, sm.probe);
+  const int ranges = aligned ? p.aligned_ranges : p.ranges;     // waves that take part
+  const int per = max(1, ceil_div(total, aligned ? kAlignedPieces * ranges : ranges));
+  if (blockIdx.x == 0 && lane == 0) *p.plan = make_int2(aligned, per);
+
+  // the sequence's slots: its pieces are numbered from here
+  auto piece_base = [&](int r) {
+    int t = 0;
+    for (int s = 0; s < r; s += 64) t += wave_total(s + lane < r ? ceil_div(units_at(p, s + lane), per) : 0);
+    return t;
+  };
+  // aligned pieces in order of (piece, sequence): the wave's are w, w + ranges, ...
+  int rank = 0, piece = 0;
+  auto aligned_piece = [&](RangeCursor& c) {
+    for (;; ++piece) {
+      int count = 0;
+      for (int s = 0; s < p.batch; s += 64)
+        count += __builtin_popcountll(__builtin_amdgcn_ballot_w64(units_at(p, s + lane) > piece * per));
+      if (count == 0) {
+        c.valid = false;
+        return;
+      }
+      if (rank < count) break;
+      rank -= count;
+    }
+    int before = 0;
+    for (int s = 0; s < p.batch; s += 64) {
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(units_at(p, s + lane) > piece * per);
+      const int n = __builtin_popcountll(mask);
+      if (rank < before + n) {
+        const int mine = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+        const bool hit = ((mask >> lane) & 1) && mine == rank - before;
+        c.r = s + __builtin_ctzll(__builtin_amdgcn_ballot_w64(hit));
+        break;
+      }
+      before += n;
+    }
+    c.len = lens_c[c.r];
+    c.x = piece * per;
+    c.xe = min(units_of(c.len), c.x + per);
+    c.slot = units_of(c.len) <= per ? -1 : piece_base(c.r) + piece;
+    c.valid = true;
+  };
+  // contiguous ranges: `left` units of the range lie past the cursor's piece
+  int left = 0;
+  auto contiguous_piece = [&](RangeCursor& c) {      // from unit c.x of sequence c.r on
+    const int n = units_of(c.len);
+    c.xe = min(n, c.x + left);
+    left -= c.xe - c.x;
+    c.slot = (c.x == 0 && c.xe == n) ? -1 : c.r + w;
+    c.valid = true;
+  };
+
+  RangeCursor ids{};
+  if (w >= ranges) return;
+  if (aligned) {
+    rank = w;
+    aligned_piece(ids);
+  } else {
+    const int u = w * per;
+    left = min(total, u + per) - u;
+    if (left > 0) {
+      int first = 0;                                    // first unit of sequence ids.r
+      for (int s = 0;; s += 64) {
+        const int n = units_at(p, s + lane);
+        const int incl = wave_scan(n);
+        const unsigned long long past = __builtin_amdgcn_ballot_w64(first + incl > u);
+        if (past != 0) {
+          const int l = __builtin_ctzll(past);
+          ids.r = s + l;
+          first += __builtin_amdgcn_readlane(incl - n, l);
+          break;
+        }
+        first += __builtin_amdgcn_readlane(incl, 63);
+      }
+      ids.len = lens_c[ids.r];
+      ids.x = u - first;
+      contiguous_piece(ids);
+    }
+  }
+  if (!ids.valid) return;
+  // the unit after the cursor's: in its piece, or the first of the next one
+  auto advance = [&](RangeCursor& c, auto tag) {
+    if (++c.x < c.xe) return;
+    if constexpr (decltype(tag)::value) {
+      rank += ranges;
+      aligned_piece(c);
+      return;
+    }
+    if (left <= 0) {
+      c.valid = false;
+      return;
+    }
+    do c.len = lens_c[++c.r];
+    while (c.len <= 0);
+    c.x = 0;
+    contiguous_piece(c);
+  };
+
+  const size_t tile_elems = (size_t)kBlock * D;
+  const size_t slot_elems = (size_t)p.num_kv_heads * tile_elems;
+  const uint16_t* kbase = p.k_pool + (size_t)g * tile_elems;
+  const uint16_t* vbase = p.v_pool + (size_t)g * tile_elems;
+  const bool head_valid = j < p.group;
+  const int h = g * p.group + (head_valid ? j : 0);
+  const float c = p.scale_log2;
+
+  bf16x8 kreg[2][DC];
+  bf16x8 vreg[kVLoads];
+  // K fragments (A operand) and V rows of the blocks id0, id1, through buffer
+  // descriptors over the (block, head) tiles (the per-lane offsets are the
+  // same for every tile).  Where each block is read once V is loaded
+  // non-temporally, so that half the stream leaves the last-level cache alone
+  const int k_off = 2 * (j * D + 8 * qd);
+  const int v_off = 16 * lane;
+  auto load_chunk = [&](int id0, int id1, auto tag) {
+    constexpr int kVPolicy = decltype(tag)::value ? 0 : kNonTemporal;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+      const size_t at = (size_t)(mt ? id1 : id0) * slot_elems;
+      const __amdgpu_buffer_rsrc_t krs =
+          __builtin_amdgcn_make_buffer_rsrc((void*)(kbase + at), (short)0, kTileBytes, kRawBufferWord3);
+      const __amdgpu_buffer_rsrc_t vrs =
+          __builtin_amdgcn_make_buffer_rsrc((void*)(vbase + at), (short)0, kTileBytes, kRawBufferWord3);
+#pragma unroll
+      for (int dc = 0; dc < DC; ++dc)
+        kreg[mt][dc] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(krs, k_off + 64 * dc, 0, 0));
+#pragma unroll
+      for (int v = 0; v < kVLoads / 2; ++v)
+        vreg[mt * (kVLoads / 2) + v] =
+            __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vrs, v_off + 1024 * v, 0, kVPolicy));
+    }
+  };
+  // block ids of a cursor's unit; past the sequence's end its last block again
+  // (its keys there are masked, its V rows zeroed)
+  auto ids_of = [&](const RangeCursor& cu, int& id0, int& id1) {
+    const ScalarInts bt = (ScalarInts)(p.block_tables + (size_t)cu.r * p.max_blocks_per_seq);
+    const int b0 = cu.x * kUnitBlocks;
+    id0 = bt[b0];
+    id1 = bt[min(b0 + 1, (cu.len - 1) / kBlock)];
+  };
+  // V^T fragment (16 dims x 32 keys), as in paged_decode_attn_kernel
+  const int tr_off = (4 * qd + (j >> 2)) * vStride + 4 * (j & 3);
+  auto v_frag = [&](int dt) -> bf16x8 {
+    const uint16_t* base = sm.v + tr_off + 16 * dt;
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base + 16 * vStride));
+    const i16x4 lohi[2] = {lo, hi};
+    return __builtin_bit_cast(bf16x8, lohi);
+  };
+  bf16x8 qreg[DC];
+  auto load_q = [&](int r) {
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) {
+      qreg[dc] = bf16x8{};
+      if (head_valid)
+        qreg[dc] = *reinterpret_cast<const bf16x8*>(p.q + ((size_t)r * p.num_q_heads + h) * D + 32 * dc + 8 * qd);
+    }
+  };
+
+  f32x4 oacc[DT];
+  float m_run, l_run;
+  auto reset = [&]() {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) oacc[dt] = f32x4{};
+    m_run = -INFINITY;
+    l_run = 0.f;
+  };
+
+  // three cursors: the unit being computed, the one whose loads are in flight
+  // behind it, and the one whose block ids are being read
+  auto run = [&](auto tag) __attribute__((always_inline)) {
+    RangeCursor cur = ids;
+    int id0, id1;
+    ids_of(cur, id0, id1);
+    load_q(cur.r);
+    load_chunk(id0, id1, tag);
+    reset();
+    advance(ids, tag);
+    RangeCursor nxt = ids;
+    if (nxt.valid) ids_of(nxt, id0, id1);
+
+    for (;;) {
+      const int key0 = cur.x * kUnitKeys;
+  #pragma unroll
+      for (int v = 0; v < kVLoads; ++v) {
+        const int cc = lane + 64 * v;
+        *reinterpret_cast<bf16x8*>(&sm.v[(cc / kRowChunks) * vStride + (cc % kRowChunks) * 8]) = vreg[v];
+      }
+      // rows past the end of the sequence (inside its last block) hold zeros:
+      // their probabilities are 0, but 0 times a stale NaN or Inf is NaN
+      if (key0 + kChunk > cur.len) {
+  #pragma unroll
+        for (int v = 0; v < kVLoads; ++v) {
+          const int cc = lane + 64 * v;
+          if (key0 + cc / kRowChunks >= cur.len)
+            *reinterpret_cast<bf16x8*>(&sm.v[(cc / kRowChunks) * vStride + (cc % kRowChunks) * 8]) = bf16x8{};
+        }
+      }
+      f32x4 s[2] = {f32x4{}, f32x4{}};
+  #pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+  #pragma unroll
+        for (int dc = 0; dc < DC; ++dc)
+          s[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kreg[mt][dc], qreg[dc], s[mt], 0, 0, 0);
+      // the next unit's loads, in flight during the math; block ids one further
+      if (nxt.valid) {
+        load_chunk(id0, id1, tag);
+        advance(ids, tag);
+        if (ids.valid) ids_of(ids, id0, id1);
+      }
+      float mloc = -INFINITY;
+  #pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+  #pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          const int key = key0 + 16 * mt + 4 * qd + rr;
+          s[mt][rr] = key < cur.len ? s[mt][rr] : -INFINITY;
+          mloc = fmaxf(mloc, s[mt][rr]);
+        }
+      mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
+      mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+      const float m_new = fmaxf(m_run, mloc);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+      m_run = m_new;
+      l_run *= alpha;
+  #pragma unroll
+      for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
+      const float mc = m_new * c;
+      bf16x8 pb;
+  #pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+  #pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mt][rr], c, -mc));
+          pb[4 * mt + rr] = (__bf16)e;
+          l_run += (float)pb[4 * mt + rr];
+        }
+  #pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v_frag(dt), pb, oacc[dt], 0, 0, 0);
+
+      if (cur.x + 1 == cur.xe) {
+        // the piece ends: lane (j, qd) holds dims 16 dt + 4 qd .. +3 of head j
+        if (nxt.valid) load_q(nxt.r);
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+        if (head_valid) {
+          if (cur.slot < 0) {
+            uint16_t* orow = p.out + ((size_t)cur.r * p.num_q_heads + h) * D;
+  #pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+              bf16x4 o;
+  #pragma unroll
+              for (int e = 0; e < 4; ++e) o[e] = (__bf16)(oacc[dt][e] / l_run);
+              *reinterpret_cast<uint2*>(orow + 16 * dt + 4 * qd) = __builtin_bit_cast(uint2, o);
+            }
+          } else {
+            const size_t at = ((size_t)g * p.slots + cur.slot) * p.group + j;
+  #pragma unroll
+            for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(p.ws_o + at * D + 16 * dt + 4 * qd) = oacc[dt];
+            if (qd == 0) *reinterpret_cast<float2*>(p.ws_ml + 2 * at) = make_float2(m_run, l_run);
+          }
+        }
+        if (!nxt.valid) return;
+        reset();
+      }
+      cur = nxt;
+      nxt = ids;
+    }
+  };
+  if (aligned)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
+}
+
+// One work-group per (sequence, KV head): combines the pieces that
+// decode_ranges_kernel left of a sequence (a sequence of one piece has its
+// output already).  A thread holds four features of one row; as many teams of
+// threads as fit share the pieces, each taking kMergeStep at a time so that
+// their loads are in flight together, and the teams' results meet in LDS.
+// The launch is one chain of memory latencies (lengths and plan, pieces,
+// output), so what counts is that there are few of them.
+constexpr int kMergeStep = 8;
+constexpr int kMergeThreads = 512;     // kMaxGroup * 128 / 4
+template <int D>
+__global__ __launch_bounds__(kMergeThreads) void decode_ranges_merge_kernel(DecParams p) {
+  __shared__ f32x4 team_acc[kMergeThreads];
+  __shared__ float2 team_md[kMergeThreads];
+  const int lane = threadIdx.x & 63;
+  const int g = blockIdx.x % p.num_kv_heads;
+  const int r = blockIdx.x / p.num_kv_heads;
+  const int2 plan = *p.plan;
+  const bool aligned = plan.x != 0;
+  const int per = plan.y;
+  // units before r, or (aligned) pieces before r
+  int before = 0;
+  for (int s = 0; s < r; s += 64) {
+    const int x = s + lane < r ? units_of(p.seq_lens[s + lane]) : 0;
+    before += wave_total(aligned ? ceil_div(x, per) : x);
+  }
+  const int units = units_of(p.seq_lens[r]);
+  int first, n;                          // the sequence's first slot, and its pieces
+  if (aligned) {
+    first = before;
+    n = ceil_div(units, per);
+  } else {
+    const int w0 = before / per;
+    first = r + w0;
+    n = (before + units - 1) / per - w0 + 1;
+  }
+  if (n <= 1) return;
+  const float c = p.scale_log2;
+  const int elems = p.group * (D / 4);   // threads of a team
+  const int teams = kMergeThreads / elems;
+  const int team = threadIdx.x / elems;
+  const int idx = threadIdx.x - team * elems;
+  const int hj = idx / (D / 4);
+  const int d = idx % (D / 4) * 4;
+  float mx = -INFINITY, den = 0.f;
+  f32x4 acc = f32x4{};
+  if (team < teams) {
+    const size_t base = ((size_t)g * p.slots + first) * p.group + hj;
+    for (int i = team; i < n; i += kMergeStep * teams) {
+      float2 ml[kMergeStep];
+      f32x4 o[kMergeStep];
+#pragma unroll
+      for (int x = 0; x < kMergeStep; ++x) {
+        // past the last piece: the last one again, with weight 0
+        const size_t at = base + (size_t)min(i + x * teams, n - 1) * p.group;
+        ml[x] = *reinterpret_cast<const float2*>(p.ws_ml + 2 * at);
+        o[x] = *reinterpret_cast<const f32x4*>(p.ws_o + at * D + d);
+      }
+      float m_new = mx;
+#pragma unroll
+      for (int x = 0; x < kMergeStep; ++x) m_new = fmaxf(m_new, ml[x].x);
+      const float alpha = __builtin_amdgcn_exp2f((mx - m_new) * c);
+      mx = m_new;
+      acc *= alpha;
+      den *= alpha;
+#pragma unroll
+      for (int x = 0; x < kMergeStep; ++x) {
+        const float wt = i + x * teams < n ? __builtin_amdgcn_exp2f((ml[x].x - mx) * c) : 0.f;
+        acc += wt * o[x];
+        den += wt * ml[x].y;
+      }
+    }
+  }
+  team_acc[threadIdx.x] = acc;
+  team_md[threadIdx.x] = make_float2(mx, den);
+  __syncthreads();
+  if (team != 0) return;
+  float m_all = mx;
+  for (int t = 1; t < teams; ++t) m_all = fmaxf(m_all, team_md[t * elems + idx].x);
+  const float w_own = __builtin_amdgcn_exp2f((mx - m_all) * c);
+  acc *= w_own;
+  den *= w_own;
+  for (int t = 1; t < teams; ++t) {
+    const float2 md = team_md[t * elems + idx];
+    const float wt = __builtin_amdgcn_exp2f((md.x - m_all) * c);      // 0 for a team without pieces
+    acc += wt * team_acc[t * elems + idx];
+    den += wt * md.y;
+  }
+  const size_t row = (size_t)r * p.num_q_heads + g * p.group + hj;
+  bf16x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[e] / den);
+  *reinterpret_cast<uint2*>(p.out + row * D + d) = __builtin_bit_cast(uint2, o);
+}
+
 // One work-group per (sequence, KV head): the final output of cascade decode
 // from every partial of the row (shared-prefix chunks, own-key segments).
 // The maxima and sums of all partials are gathered into LDS by all threads
@@ -412,8 +921,27 @@ __global__ __launch_bounds__(kThreads) void cascade_merge_kernel(DecParams p) {
 
 }  // namespace
 
+// Ranges or one work-group per (sequence, KV head): ranges win from a few
+// hundred keys on, at every batch.  32 / 8 heads of 128, us a call, one
+// work-group per pair -> ranges (with their merge): 1 sequence of 500-900 keys
+// 16.3 -> 8.0, 3 of 2000-6000 57 -> 19, 24 of 500-9000 123 -> 85, 64 of
+// 6000-9000 334 -> 308, 128 of 100-500 72 -> 36, 512 of 1000-2000 769 -> 507.
+// Below, and at head_dim 64 up to 512 keys while the pairs fit one round, the
+// merge launch is not paid for (8 sequences of 100-500 keys at 64: 8.5 -> 8.6,
+// 16 of them 8.9 -> 10.3 before the loads went through descriptors).
+DecodeGeometry decode_geometry(int batch, int max_seq_len, int num_kv_heads, int head_dim, int cus) {
+  DecodeGeometry geo = {};
+  if (batch < 1 || batch > kRangeMaxBatch || max_seq_len <= 128) return geo;
+  if (head_dim == 64 && max_seq_len <= 512 && (long long)batch * num_kv_heads <= cus) return geo;
+  const int groups_per_cu = head_dim == 128 ? kRangeGroupsPerCu128 : kRangeGroupsPerCu64;
+  geo.ranges = std::max(1, groups_per_cu * cus / num_kv_heads);
+  geo.aligned_ranges = std::max(1, kAlignedGroupsPerCu * cus / num_kv_heads);
+  geo.slots = std::max(geo.ranges, kAlignedPieces * geo.aligned_ranges) + batch;
+  return geo;
+}
+
 hipError_t launch_paged_decode_attn(const DecodeLaunch& a, hipStream_t stream) {
-  DecParams p;
+  DecParams p = {};
   p.q = a.q;
   p.k_pool = a.k_pool;
   p.v_pool = a.v_pool;
@@ -426,7 +954,25 @@ hipError_t launch_paged_decode_attn(const DecodeLaunch& a, hipStream_t stream) {
   p.group = a.num_q_heads / a.num_kv_heads;
   p.scale_log2 = a.scale * kLog2e;
   p.batch = a.batch;
-  const dim3 grid((unsigned)((long long)a.batch * a.num_kv_heads)), block(64 * kDecodeWaves);
+  const unsigned rows = (unsigned)((long long)a.batch * a.num_kv_heads);
+  if (a.ranges > 0) {
+    p.ranges = a.ranges;
+    p.aligned_ranges = a.aligned_ranges;
+    p.slots = a.slots;
+    p.ws_o = static_cast<float*>(a.workspace);
+    p.ws_ml = p.ws_o + (size_t)a.slots * a.num_q_heads * a.head_dim;
+    p.plan = reinterpret_cast<int2*>(p.ws_ml + (size_t)a.slots * a.num_q_heads * 2);
+    const dim3 grid((unsigned)(std::max(a.ranges, a.aligned_ranges) * a.num_kv_heads)), block(64);
+    if (a.head_dim == 128) {
+      hipLaunchKernelGGL(decode_ranges_kernel<128>, grid, block, 0, stream, p);
+      hipLaunchKernelGGL(decode_ranges_merge_kernel<128>, dim3(rows), dim3(kMergeThreads), 0, stream, p);
+    } else {
+      hipLaunchKernelGGL(decode_ranges_kernel<64>, grid, block, 0, stream, p);
+      hipLaunchKernelGGL(decode_ranges_merge_kernel<64>, dim3(rows), dim3(kMergeThreads), 0, stream, p);
+    }
+    return hipGetLastError();
+  }
+  const dim3 grid(rows), block(64 * kDecodeWaves);
   if (a.head_dim == 128) {
     hipLaunchKernelGGL((paged_decode_attn_kernel<128, false>), grid, block, 0, stream, p);
   } else {

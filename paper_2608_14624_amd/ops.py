@@ -33,7 +33,8 @@ EXPORTED = ("cs_prefill_paged_attn", "cs_kv_prefetch", "cs_kv_write", "cs_kv_off
             "cs_scout_survival_all", "cs_scout_observe_touches", "cs_cascade_decode_attn",
             "cs_cascade_decode_workspace_bytes", "cs_prefill_paged_attn_launch_shape",
             "cs_source_digest", "cs_cascade_decode_attn_noalloc", "cs_prefill_paged_attn_ws",
-            "cs_prefill_paged_attn_workspace_bytes")
+            "cs_prefill_paged_attn_workspace_bytes", "cs_paged_decode_attn_ws",
+            "cs_paged_decode_workspace_bytes")
 
 # bytes of the device scratch array behind cs_cascade_decode_attn_noalloc
 NOALLOC_SCRATCH_BYTES = 32 * 1024 * 1024
@@ -76,6 +77,11 @@ def _load():
     lib.cs_paged_decode_attn.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32,
                                          i32, f32, vp, vp]
     lib.cs_paged_decode_attn.restype = ctypes.c_int
+    lib.cs_paged_decode_attn_ws.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32,
+                                            i32, f32, vp, ctypes.c_int64, vp, vp]
+    lib.cs_paged_decode_attn_ws.restype = ctypes.c_int
+    lib.cs_paged_decode_workspace_bytes.argtypes = [i32, i32, i32, i32, i32, i32]
+    lib.cs_paged_decode_workspace_bytes.restype = ctypes.c_int64
     lib.cs_cascade_decode_attn.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, vp, vp, i32,
                                            i32, i32, i32, i32, i32, i32, i32, f32, vp,
                                            ctypes.c_int64, vp, vp]
@@ -177,6 +183,19 @@ def cs_kv_prefetch_raw(host_k, host_v, dst_block_ids, n, k_pool, v_pool, num_blo
     """The C call with raw pointers (ints or None); returns the status code."""
     return _lib.cs_kv_prefetch(host_k, host_v, dst_block_ids, n, k_pool, v_pool, num_blocks,
                                num_kv_heads, head_dim, block_size, stream)
+
+
+def _scratch(nbytes, stream, device):
+    """A new uint8 GPU tensor for work on ``stream`` (None: the current
+    stream).  It comes from the allocator's pool of that very stream, so its
+    memory is neither still in use by work on another stream nor given back
+    before the stream has passed the work that uses it."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if isinstance(stream, int):
+        stream = torch.cuda.ExternalStream(stream, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
 def _require(cond, msg):
@@ -413,10 +432,33 @@ def cs_paged_decode_attn_raw(q, k_pool, v_pool, block_tables, seq_lens, batch, m
                                      out, stream)
 
 
+def cs_paged_decode_attn_ws_raw(q, k_pool, v_pool, block_tables, seq_lens, batch, max_seq_len,
+                                max_blocks_per_seq, num_blocks, num_q_heads, num_kv_heads,
+                                head_dim, block_size, scale, workspace, workspace_bytes, out,
+                                stream=0):
+    """The C call with a workspace, raw pointers (ints or None); returns the status code."""
+    return _lib.cs_paged_decode_attn_ws(q, k_pool, v_pool, block_tables, seq_lens, batch,
+                                        max_seq_len, max_blocks_per_seq, num_blocks, num_q_heads,
+                                        num_kv_heads, head_dim, block_size, ctypes.c_float(scale),
+                                        workspace, workspace_bytes, out, stream)
+
+
+def paged_decode_workspace_bytes(batch, max_seq_len, num_q_heads, num_kv_heads, head_dim,
+                                 num_cus=0):
+    """Bytes of workspace ``cs_paged_decode_attn_ws`` takes (0: one work-group
+    per sequence and KV head, no partial results; negative: bad arguments, or
+    no GPU to size for)."""
+    return int(_lib.cs_paged_decode_workspace_bytes(batch, max_seq_len, num_q_heads, num_kv_heads,
+                                                    head_dim, num_cus))
+
+
 def cs_paged_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, out, *, max_seq_len, scale,
                          stream=None):
     """Enqueue paged decode attention: ``q``/``out`` bf16 ``[B, Hq, D]``,
-    ``seq_lens`` int32 ``[B]``, pools and block tables as for prefill."""
+    ``seq_lens`` int32 ``[B]``, pools and block tables as for prefill.  The
+    workspace of ``cs_paged_decode_attn_ws`` is allocated here, from the
+    caching allocator's pool of the launch's stream (the C call itself
+    allocates nothing)."""
     dev = q.device
     for name, t, dt in (("q", q, torch.bfloat16), ("k_pool", k_pool, torch.bfloat16),
                         ("v_pool", v_pool, torch.bfloat16), ("out", out, torch.bfloat16),
@@ -432,10 +474,16 @@ def cs_paged_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, out, *, max_
     _require(d == d2, "head_dim of q and pools differ")
     _require(block_tables.dim() == 2 and block_tables.shape[0] == batch, "block_tables must be [B, max_blocks]")
     _require(seq_lens.numel() == batch, "seq_lens must have B entries")
-    _check(cs_paged_decode_attn_raw(_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables),
-                                    _ptr(seq_lens), batch, int(max_seq_len), block_tables.shape[1],
-                                    num_blocks, hq, hkv, d, bs, float(scale), _ptr(out),
-                                    _stream_handle(stream, dev)))
+    args = (_ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables), _ptr(seq_lens), batch,
+            int(max_seq_len), block_tables.shape[1], num_blocks, hq, hkv, d, bs,
+            ctypes.c_float(scale))
+    need = paged_decode_workspace_bytes(batch, int(max_seq_len), hq, hkv, d)
+    handle = _stream_handle(stream, dev)
+    if need > 0:
+        ws = _scratch(need, stream, dev)
+        _check(_lib.cs_paged_decode_attn_ws(*args, _ptr(ws), need, _ptr(out), handle))
+    else:
+        _check(_lib.cs_paged_decode_attn(*args, _ptr(out), handle))
 
 
 def cs_cascade_decode_attn_raw(q, k_pool, v_pool, block_tables, seq_lens, batch, max_seq_len,

@@ -1,0 +1,138 @@
+"""GPU parity of the decode launches that deal their keys to one-wave
+work-groups in ranges (cs_paged_decode_attn_ws, which ops.cs_paged_decode_attn
+calls).
+
+Sizes sit at the edges of the plan: one sequence; lengths around the 32-key
+unit and the 16-token block; many more units than ranges and fewer; sequences
+cut over many ranges beside whole ones; KV head counts that leave the ranges
+uneven; more than 64 sequences (one lane each); a bound far above the lengths;
+and the same for sequences that share their first blocks, which are cut at the
+same positions, with sharing that starts and ends around the probed block.  Each
+output is compared with the float64 oracle over every element, and with the
+one-work-group-per-pair call, whose partial sums differ only in order.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import MAX_ABS, MEAN_ABS, poison_tails
+from paper_2608_14624_amd.workload import Invocation, build_workload, decode_view
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def dev(a):
+    a = np.ascontiguousarray(a)
+    if a.dtype == np.uint16:
+        return torch.from_numpy(a.view(np.int16)).view(torch.bfloat16).cuda()
+    return torch.from_numpy(a).cuda()
+
+
+def workload(lens, hq, hkv, d, anchors=None):
+    """Sequences of ``lens`` keys, sequence i the agent i's alone; with
+    ``anchors``, agent i % len(anchors)'s, whose anchor of that many tokens it
+    shares (its own keys: ``lens``)."""
+    n = len(anchors) if anchors else len(lens)
+    invs = [Invocation(i % n, x) for i, x in enumerate(lens)]
+    blocks = sum(-(-x // 16) + 1 for x in lens) + sum(-(-a // 16) for a in anchors or []) + 2
+    return build_workload("ranges", 81, anchors or [0] * n, invs, num_q_heads=hq, num_kv_heads=hkv,
+                          head_dim=d, num_blocks=blocks)
+
+
+def bits(t):
+    return t.view(torch.int16).cpu().numpy().view(np.uint16)
+
+
+# name: lengths, Hq, Hkv, D, bound on the lengths (None: the longest)[, anchors]
+CASES = {
+    "one_sequence": ([5000], 32, 8, 128, None),
+    "one_short_sequence_loose_bound": ([1], 8, 2, 64, 8192),
+    "unit_edges": ([127, 128, 129, 31, 32, 33, 255, 256, 257, 15, 16, 17, 500], 32, 8, 128, None),
+    "unit_edges_d64": ([127, 128, 129, 31, 32, 33, 255, 256, 257, 15, 16, 17, 500], 8, 2, 64, 600),
+    "long_beside_short": ([1, 9000, 3, 700, 1], 16, 4, 128, None),
+    "more_units_than_ranges": ([3000 + 311 * i for i in range(17)], 12, 3, 128, None),
+    "one_kv_head_group_16": ([600, 2500, 40], 16, 1, 128, None),
+    "group_1": ([900, 10, 1300], 6, 6, 64, None),
+    "past_one_wave_of_lengths": ([1 + (37 * i) % 600 for i in range(150)], 4, 2, 64, None),
+    "loose_bound": ([300, 1200, 77], 32, 8, 128, 131072),
+    "shared_two": ([1, 2000], 32, 8, 128, None, [4000]),
+    "shared_agents": ([5 + (131 * i) % 900 for i in range(40)], 32, 8, 128, None, [1531, 3000, 64]),
+    "shared_past_one_wave": ([1 + (37 * i) % 300 for i in range(130)], 4, 4, 64, None, [700, 512]),
+    "shared_at_the_probed_block": ([1, 16, 40], 8, 2, 128, None, [512]),
+    "shared_short_of_the_probed_block": ([600, 700, 800], 8, 2, 128, None, [496]),
+    "shared_group_16": ([30, 700, 9], 16, 1, 128, 40000, [2100]),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_ranges_match_oracle(name):
+    from paper_2608_14624_amd import ops
+    lens, hq, hkv, d, bound = CASES[name][:5]
+    wl = workload(lens, hq, hkv, d, *CASES[name][5:])
+    q, seq_lens = decode_view(wl)
+    assert poison_tails(wl) > 0 or all(n % 16 == 0 for n in seq_lens)
+    bound = bound or int(seq_lens.max())
+    bt = wl.block_tables
+    if bound > bt.shape[1] * 16:     # entries past a sequence's last block are not used
+        bt = np.concatenate([bt, np.full((len(lens), -(-bound // 16) - bt.shape[1]), -1, np.int32)], 1)
+    need = ops.paged_decode_workspace_bytes(len(lens), bound, hq, hkv, d)
+    print(f"[case] ranges {name}: B={len(lens)} Hq={hq} Hkv={hkv} D={d} workspace={need}", flush=True)
+    assert need > 0
+    args = (dev(q), dev(wl.k_pool), dev(wl.v_pool), dev(bt), dev(seq_lens))
+    out = torch.full_like(args[0], float("nan"))
+    ops.cs_paged_decode_attn(*args, out, max_seq_len=bound, scale=wl.scale)
+    plain = torch.full_like(out, float("nan"))
+    p = [t.data_ptr() for t in args]
+    assert ops.cs_paged_decode_attn_raw(*p, len(lens), bound, bt.shape[1], wl.num_blocks, hq, hkv, d,
+                                        16, wl.scale, plain.data_ptr()) == ops.CS_OK
+    torch.cuda.synchronize()
+    samples = [(r, h, 0) for r in range(wl.batch) for h in range(hq)]
+    ref = oracle.prefill_paged_attn_rows(q, wl.k_pool, wl.v_pool, wl.block_tables,
+                                         seq_lens.astype(np.int32) - 1,
+                                         np.arange(wl.batch + 1, dtype=np.int32), hq, hkv, wl.scale,
+                                         samples).reshape(wl.batch, hq, d)
+    got = oracle.bf16_bits_to_f64(bits(out))
+    assert np.isfinite(got).all()
+    err = np.abs(got - ref)
+    print(f"    vs oracle max_abs={err.max():.3e} mean_abs={err.mean():.3e}", flush=True)
+    assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+    # the same bf16 products and probabilities up to each one's rounding against
+    # another reference maximum: a few bf16 ulps of values of at most about 4
+    assert np.abs(got - oracle.bf16_bits_to_f64(bits(plain))).max() <= MAX_ABS
+
+
+@pytest.mark.parametrize("anchors", [None, [800]])
+def test_ranges_on_another_stream_and_in_a_graph(anchors):
+    """The workspace comes from the pool of the launch's stream: calls on two
+    streams at once, and replays of a captured call, give the eager bits."""
+    from paper_2608_14624_amd import ops
+    wl = workload([1500, 4100, 90], 32, 8, 128, anchors)
+    q, seq_lens = decode_view(wl)
+    args = (dev(q), dev(wl.k_pool), dev(wl.v_pool), dev(wl.block_tables), dev(seq_lens))
+    kw = dict(max_seq_len=int(seq_lens.max()), scale=wl.scale)
+    want = torch.empty_like(args[0])
+    ops.cs_paged_decode_attn(*args, want, **kw)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [torch.full_like(want, float("nan")) for _ in range(8)]
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        s = streams[i % 2]
+        ops.cs_paged_decode_attn(*args, o, stream=s if i < 4 else s.cuda_stream, **kw)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o.view(torch.int16), want.view(torch.int16)) for o in outs)
+    graph = torch.cuda.CUDAGraph()
+    out = torch.empty_like(want)
+    with torch.cuda.graph(graph):
+        ops.cs_paged_decode_attn(*args, out, **kw)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        eager = torch.empty_like(want)
+        ops.cs_paged_decode_attn(*args, eager, **kw)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+        assert torch.equal(eager.view(torch.int16), want.view(torch.int16))
