@@ -149,7 +149,7 @@ int cs_prefill_paged_attn(const void *q, const void *k_pool, const void *v_pool,
  *
  * When a call of cs_prefill_paged_attn would run its split kernel on at most
  * half as many 128-row tiles as there are compute units, this call cuts
- * every tile's key steps into `parts` contiguous pieces (2 to 4: as many as
+ * every tile's key steps into `parts` contiguous pieces (2 to 16: as many as
  * fit one round of one work-group per CU, each at least four 64-key steps
  * of the longest sequence, which must have at least 16) that run on
  * separate work-groups; each writes its rows' partial result (O relative to

@@ -31,7 +31,7 @@ struct AttnLaunch {
 // most key parts a split launch takes (work-groups per tile), the fewest
 // 64-key steps of the longest sequence per part, and the fewest steps of
 // the longest sequence for a launch to take parts at all
-constexpr int kMaxKeyParts = 4;
+constexpr int kMaxKeyParts = 16;
 constexpr int kMinPartSteps = 4;
 constexpr int kMinPartedSteps = 16;
 

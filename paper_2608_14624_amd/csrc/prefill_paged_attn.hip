@@ -51,8 +51,8 @@
 // nothing to hide its softmax behind.  Instead 8 waves run each tile: waves
 // w and w + 4 own the same rows, waves 0-3 take the first half of the key
 // steps and waves 4-7 the second, each half with its own LDS ring, and at
-// the end waves 4-7 hand (O, m, l) to waves 0-3 through LDS, which merge
-// them with the log-sum-exp weights.  A ping-pong launch whose last round
+// the end the two waves of a pair exchange half of their O through LDS and
+// each merges and stores the other half with the log-sum-exp weights.  A ping-pong launch whose last round
 // would be at most half full runs that round's tiles the same way, as two
 // 128-row halves each, so it occupies every CU.  Launches that leave half
 // the CUs idle even so can take a tile's keys in parts on more work-groups,
@@ -785,64 +785,76 @@ __device__ __forceinline__ void ppd_split_tile(const Params& p, const int wg, ui
 
   const float l_run = (l_part[0] + l_part[1]) + (l_part[2] + l_part[3]);
   float l_tot = pair_sum(l_run);
-  // ---- merge: wave w of the second half hands (O, m, l) of its rows to
-  // wave w of the first through one staging buffer (16640 bytes at head_dim
-  // 128, 8448 at 64: exactly what it takes): value e of lane l at word
-  // 64 e + l, m and l of query qi at words kMl + qi and kMl + 32 + qi
-  constexpr int kMl = DT * 16 * 64;
-  static_assert(kMl + 64 <= (kBN / DL::kRows) * DL::kGrp / 2, "merge exchange exceeds a staging buffer");
+  // ---- merge: waves w and w + 4 hold two results of the same rows.  Each
+  // finishes half of the features: wave w the first DT / 2 tiles of 32, wave
+  // w + 4 the others, so each passes the other half of its O through LDS, and
+  // its m and l (one staging buffer for the O of a pair: value e of lane l at
+  // word 64 e + l, wave w + 4's after wave w's; another for the m and l).
+  // Both waves then store, which halves the exchange and the stores of a
+  // work-group's end (about 3.5 us of the 13 us that a key part of five steps
+  // takes): an 83-token suffix on 3011 cached tokens, 8 / 1 heads, with its
+  // merge launch 18.0 -> 17.2 us, 32 / 8 heads of 64 15.5 -> 15.2 (waves 0-3
+  // merging and storing alone before).
+  constexpr int DH = DT / 2;
+  constexpr int kHalfO = DH * 16 * 64;
+  static_assert(2 * kHalfO <= (kBN / DL::kRows) * DL::kGrp / 2, "merge exchange exceeds a staging buffer");
   float* x = reinterpret_cast<float*>(wave == 0 ? k0 : wave == 1 ? k1 : wave == 2 ? v0 : v1);
-  __syncthreads();
-  if (split_half == 1) {
+  float* xml = reinterpret_cast<float*>(wave == 0 ? k2 : wave == 1 ? k3 : wave == 2 ? v2 : v3);
+  auto merge = [&](auto second_tag) __attribute__((always_inline)) {
+    constexpr bool kSecond = decltype(second_tag)::value;   // waves 4-7
+    constexpr int kMine = kSecond ? DH : 0;                 // first tile this wave finishes
+    constexpr int kGiven = kSecond ? 0 : DH;
+    __syncthreads();
+    float* give = x + (kSecond ? 0 : kHalfO);
+    const float* take = x + (kSecond ? kHalfO : 0);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int dt = 0; dt < DH; ++dt)
 #pragma unroll
-      for (int rr = 0; rr < 16; ++rr) x[(dt * 16 + rr) * 64 + lane] = oacc[dt][rr];
-    x[kMl + 32 * half + qi] = half ? l_tot : m_run;
-  }
-  __syncthreads();
-  if (split_half == 1) return;
-  const float m1 = x[kMl + qi];
-  const float l1 = x[kMl + 32 + qi];
-  const float mx = fmaxf(m_run, m1);
-  const float w0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - mx) * c);
-  const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - mx) * c);
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int rr = 0; rr < 16; ++rr) oacc[dt][rr] = w0 * oacc[dt][rr] + w1 * x[(dt * 16 + rr) * 64 + lane];
-  l_tot = w0 * l_tot + w1 * l1;
-  if constexpr (kPartial) {
-    // partial result of this key part: O relative to mx, mx and l (a row
-    // whose keys in this part are all masked stores O = 0, -inf, 0)
-    if (row_valid) {
+      for (int rr = 0; rr < 16; ++rr) give[(dt * 16 + rr) * 64 + lane] = oacc[kGiven + dt][rr];
+    xml[(kSecond ? 64 : 0) + 32 * half + qi] = half ? l_tot : m_run;
+    __syncthreads();
+    const float m0 = xml[qi], l0 = xml[32 + qi], m1 = xml[64 + qi], l1 = xml[96 + qi];
+    const float mx = fmaxf(m0, m1);
+    const float w0 = m0 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m0 - mx) * c);
+    const float w1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - mx) * c);
+    const float w_own = kSecond ? w1 : w0, w_other = kSecond ? w0 : w1;
+    const float l_all = w0 * l0 + w1 * l1;
+    if (!row_valid) return;
+    if constexpr (kPartial) {
+      // partial result of this key part: O relative to mx, mx and l (a row
+      // whose keys in this part are all masked stores O = 0, -inf, 0)
       const size_t prow = (size_t)part * p.part_rows + (size_t)(q0 + t) * p.num_q_heads + h;
       float* orow = p.ws_o + prow * D;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
+      for (int dt = 0; dt < DH; ++dt) {
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg)
-          *reinterpret_cast<float4*>(orow + dt * 32 + 8 * rg + 4 * half) =
-              make_float4(oacc[dt][rg * 4], oacc[dt][rg * 4 + 1], oacc[dt][rg * 4 + 2], oacc[dt][rg * 4 + 3]);
+        for (int rg = 0; rg < 4; ++rg) {
+          float o[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            o[u] = w_own * oacc[kMine + dt][rg * 4 + u] + w_other * take[(dt * 16 + rg * 4 + u) * 64 + lane];
+          *reinterpret_cast<float4*>(orow + (kMine + dt) * 32 + 8 * rg + 4 * half) = make_float4(o[0], o[1], o[2], o[3]);
+        }
       }
-      if (half == 0) *reinterpret_cast<float2*>(p.ws_ml + 2 * prow) = make_float2(mx, l_tot);
-    }
-    return;
-  }
-  const float inv = 1.f / l_tot;
-  if (row_valid) {
-    uint16_t* orow = p.out + qrow;
+      if (!kSecond && half == 0) *reinterpret_cast<float2*>(p.ws_ml + 2 * prow) = make_float2(mx, l_all);
+    } else {
+      const float inv = 1.f / l_all;
+      uint16_t* orow = p.out + qrow;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
+      for (int dt = 0; dt < DH; ++dt) {
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        bf16x4 o;
+        for (int rg = 0; rg < 4; ++rg) {
+          bf16x4 o;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) o[u] = (__bf16)(oacc[dt][rg * 4 + u] * inv);
-        *reinterpret_cast<uint2*>(orow + dt * 32 + 8 * rg + 4 * half) = __builtin_bit_cast(uint2, o);
+          for (int u = 0; u < 4; ++u)
+            o[u] = (__bf16)((w_own * oacc[kMine + dt][rg * 4 + u] + w_other * take[(dt * 16 + rg * 4 + u) * 64 + lane]) * inv);
+          *reinterpret_cast<uint2*>(orow + (kMine + dt) * 32 + 8 * rg + 4 * half) = __builtin_bit_cast(uint2, o);
+        }
       }
     }
-  }
+  };
+  if (split_half) merge(std::true_type{});
+  else merge(std::false_type{});
 }
 
 // The ping-pong kernel (D = 128 and 64).  K and V go straight from HBM into
@@ -1210,7 +1222,12 @@ __global__ __launch_bounds__(kPPThreads, D == 64 ? 4 : 2) void prefill_paged_att
 // sum_p w_p l_p, rounded to bf16.  Part 0 holds key 0, which every row sees,
 // so the sum of weights is never empty.  D / 4 threads per row, four
 // consecutive features each.
-template <int D>
+// The loads of kStep parts (2, 4 or 8: the fewest that hold the launch's
+// parts, so that few are read twice) are in flight together, where a loop over
+// single parts waited for each in turn: calls with 4 to 8 parts 23.1 -> 20.9 us
+// (2656 rows of 128), 22.9 -> 20.0 (512 rows), 20.5 -> 18.0 (664 rows); past the
+// last part the last one is read again, with weight 0.
+template <int D, int kStep>
 __global__ __launch_bounds__(kThreads) void prefill_split_merge_kernel(Params p) {
   constexpr int kTpr = D / 4;
   constexpr int kRowsPerBlock = kThreads / kTpr;
@@ -1219,19 +1236,37 @@ __global__ __launch_bounds__(kThreads) void prefill_split_merge_kernel(Params p)
   const int d0 = (threadIdx.x % kTpr) * 4;
   const float c = p.scale_log2;
   float mx = -INFINITY;
-  for (int q = 0; q < p.parts; ++q) mx = fmaxf(mx, p.ws_ml[2 * ((size_t)q * p.part_rows + row)]);
   float den = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int q = 0; q < p.parts; ++q) {
-    const size_t prow = (size_t)q * p.part_rows + row;
-    const float2 ml = *reinterpret_cast<const float2*>(p.ws_ml + 2 * prow);
-    const float w = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml.x - mx) * c);
-    const float4 o = *reinterpret_cast<const float4*>(p.ws_o + prow * D + d0);
-    den += w * ml.y;
-    acc.x += w * o.x;
-    acc.y += w * o.y;
-    acc.z += w * o.z;
-    acc.w += w * o.w;
+  for (int q0 = 0; q0 < p.parts; q0 += kStep) {
+    float2 ml[kStep];
+    float4 o[kStep];
+#pragma unroll
+    for (int q = 0; q < kStep; ++q) {
+      const size_t prow = (size_t)min(q0 + q, p.parts - 1) * p.part_rows + row;
+      ml[q] = *reinterpret_cast<const float2*>(p.ws_ml + 2 * prow);
+      o[q] = *reinterpret_cast<const float4*>(p.ws_o + prow * D + d0);
+    }
+    float m_new = mx;
+#pragma unroll
+    for (int q = 0; q < kStep; ++q) m_new = fmaxf(m_new, ml[q].x);
+    // -inf while no part so far has held a key of the row
+    const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mx - m_new) * c);
+    mx = m_new;
+    den *= alpha;
+    acc.x *= alpha;
+    acc.y *= alpha;
+    acc.z *= alpha;
+    acc.w *= alpha;
+#pragma unroll
+    for (int q = 0; q < kStep; ++q) {
+      const float w = (q0 + q >= p.parts || ml[q].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((ml[q].x - mx) * c);
+      den += w * ml[q].y;
+      acc.x += w * o[q].x;
+      acc.y += w * o[q].y;
+      acc.z += w * o[q].z;
+      acc.w += w * o[q].w;
+    }
   }
   const float inv = 1.f / den;
   bf16x4 r;
@@ -1274,7 +1309,11 @@ AttnGeometry attn_geometry(int batch, int max_q_len, int max_kv_len, int num_q_h
     // round (at most kMaxKeyParts), each part at least kMinPartSteps steps of
     // the longest sequence.  (Single small launches of 5-12 steps ran 0.4-1.5
     // us slower with parts, the merge launch unpaid for; 17 steps ran 22%
-    // faster.)
+    // faster.  At most 8 and 16 parts, us a call: a 16-token suffix on 6000
+    // cached tokens, 32 / 8 heads of 128, 19.7 and 16.6; 300 tokens on 8000,
+    // 8 / 1 heads, 29.0 and 26.8; 30 tokens on 4000, 4 sequences, 23.0 and
+    // 22.9.  With at most 4, and the merge that waited for each part in turn,
+    // 29.6, 39.9 and 26.7.)
     // (Choosing the parts by the rounds they take, so that launches of more
     // than half a round split too, was slower: a part's fixed costs of Q
     // loads, pipeline fill, half merge and partial store outweigh it.)
@@ -1332,13 +1371,20 @@ hipError_t launch_prefill_paged_attn(const AttnLaunch& a, hipStream_t stream) {
     // key parts on more work-groups, then the merge of their partials
     const long long rows_per_block = kThreads / (a.head_dim / 4);
     const dim3 mgrid((unsigned)((p.part_rows + rows_per_block - 1) / rows_per_block));
-    if (a.head_dim == 128) {
-      hipLaunchKernelGGL((prefill_paged_attn_ppd_split_kernel<128, true>), grid, dim3(kPPThreads), 0, stream, p);
-      hipLaunchKernelGGL(prefill_split_merge_kernel<128>, mgrid, dim3(kThreads), 0, stream, p);
-    } else {
-      hipLaunchKernelGGL((prefill_paged_attn_ppd_split_kernel<64, true>), grid, dim3(kPPThreads), 0, stream, p);
-      hipLaunchKernelGGL(prefill_split_merge_kernel<64>, mgrid, dim3(kThreads), 0, stream, p);
-    }
+    auto merge = [&](auto d_tag) {
+      constexpr int D = decltype(d_tag)::value;
+      hipLaunchKernelGGL((prefill_paged_attn_ppd_split_kernel<D, true>), grid, dim3(kPPThreads), 0, stream, p);
+      if (geo.parts == 2)
+        hipLaunchKernelGGL((prefill_split_merge_kernel<D, 2>), mgrid, dim3(kThreads), 0, stream, p);
+      else if (geo.parts <= 4)
+        hipLaunchKernelGGL((prefill_split_merge_kernel<D, 4>), mgrid, dim3(kThreads), 0, stream, p);
+      else
+        hipLaunchKernelGGL((prefill_split_merge_kernel<D, 8>), mgrid, dim3(kThreads), 0, stream, p);
+    };
+    if (a.head_dim == 128)
+      merge(std::integral_constant<int, 128>{});
+    else
+      merge(std::integral_constant<int, 64>{});
     return hipGetLastError();
   }
   if (geo.waves == kPPWaves) {

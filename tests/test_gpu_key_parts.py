@@ -91,6 +91,22 @@ def test_key_parts_match_oracle(name, head_dim):
     check_parts(wl)
 
 
+# launches at the edges of the merge's steps of 2, 4 and 8 parts, and the most
+# parts a launch takes: (cached, suffix tokens), Hq, Hkv, parts
+PART_COUNTS = [((1200, 100), 32, 1, 5), ((1900, 58), 16, 2, 7), ((2048, 1), 8, 2, 8),
+               ((2300, 4), 8, 2, 9), ((3900, 30), 8, 4, 15), ((9000, 33), 8, 2, 16)]
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("lens,hq,hkv,parts", PART_COUNTS)
+def test_key_part_counts_match_oracle(lens, hq, hkv, parts, head_dim):
+    from paper_2608_14624_amd import ops
+    wl = build_workload("part_counts", 76, [lens[0]], [Invocation(0, lens[1])], num_q_heads=hq,
+                        num_kv_heads=hkv, head_dim=head_dim, num_blocks=1024)
+    assert parts_of(ops, wl) == parts
+    check_parts(wl)
+
+
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_key_parts_with_peaky_logits(head_dim):
     """Queries scaled up 8x (logits in the tens of log2 units): the parts'
