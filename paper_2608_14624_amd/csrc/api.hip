@@ -548,7 +548,18 @@ int cascade_decode(const void* q, const void* k_pool, const void* v_pool,
   a.num_kv_heads = num_kv_heads;
   a.head_dim = head_dim;
   a.scale = scale;
-  hipError_t e = cs::launch_shared_prefix_partials(a, s);
+  int cus = 0;
+  hipError_t e = cs::current_device_cus(&cus);
+  if (e != hipSuccess) return hip_fail(e, "compute-unit count of the current device");
+  const cs::CascadeRanges ranges =
+      cs::cascade_ranges(batch, num_groups, max_group_seqs, max_shared_len, max_rest_len, num_q_heads,
+                         num_kv_heads, head_dim, geo.chunks + geo.segments, cus);
+  if (ranges.ranges > 0) {
+    e = cs::launch_cascade_ranges(a, ranges, s);
+    if (e != hipSuccess) return hip_fail(e, "cascade decode launch");
+    return ok();
+  }
+  e = cs::launch_shared_prefix_partials(a, s);
   if (e != hipSuccess) return hip_fail(e, "shared-prefix attention launch");
   e = cs::launch_cascade_decode_rest(a, s);
   if (e != hipSuccess) return hip_fail(e, "cascade decode launch");

@@ -185,4 +185,18 @@ struct CascadeLaunch {
 hipError_t launch_shared_prefix_partials(const CascadeLaunch& a, hipStream_t stream);
 hipError_t launch_cascade_decode_rest(const CascadeLaunch& a, hipStream_t stream);
 
+// Cascade decode in ranges (cascade_ranges.hip), where the workspace of `parts`
+// chunks and segments has the room: both halves in one launch of `ranges`
+// one-wave work-groups per KV head, with `rows` partial rows per KV head
+// (ranges 0: the launches in chunks and segments).
+struct CascadeRanges {
+  int ranges;
+  int width;
+  int rows;
+};
+CascadeRanges cascade_ranges(int batch, int num_groups, int max_group_seqs, int max_shared_len,
+                             int max_rest_len, int num_q_heads, int num_kv_heads, int head_dim,
+                             long long parts, int cus);
+hipError_t launch_cascade_ranges(const CascadeLaunch& a, const CascadeRanges& geo, hipStream_t stream);
+
 }  // namespace cs

@@ -25,7 +25,8 @@
 //     current one, so each wave keeps 16 KiB in flight.
 //   * Work-groups are ordered KV head fastest, so each XCD serves one head.
 //
-// Cascade mode: a sequence belongs to a group whose shared prefix (its first
+// Cascade mode (the launches that cascade_ranges.hip does not take): a sequence
+// belongs to a group whose shared prefix (its first
 // shared_len keys) is attended by the stacked prefill kernel, which leaves
 // one partial result (O relative to its running max m, the max m and the sum
 // l) per 1024-key chunk in a workspace.  Here a work-group takes one KV head
@@ -33,6 +34,7 @@
 // a long history spreads over several work-groups, and leaves its partial
 // in the workspace too; cascade_merge_kernel then combines every partial of
 // a row with log-sum-exp weights exp2((m_i - max) * c).
+#include "decode_common.h"
 #include "internal.h"
 
 #include <math.h>
@@ -43,14 +45,6 @@
 namespace cs {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-
-constexpr int kBlock = 16;
-constexpr int kChunk = 32;           // keys per wave step (2 pool blocks)
 // waves per work-group: 12 for plain decode (one work-group fills a CU at
 // three waves per SIMD, so a CU's last, longest sequence runs on all of its
 // wave slots instead of a third of them), 4 for the cascade's 1024-key
@@ -58,10 +52,8 @@ constexpr int kChunk = 32;           // keys per wave step (2 pool blocks)
 constexpr int kDecodeWaves = 12;
 constexpr int kCascadeWaves = 4;
 constexpr int kThreads = 256;        // the merge kernel
-constexpr int kMaxGroup = 16;
 // plain decode batches up to this size run longest sequence first
 constexpr int kLptMaxBatch = 1024;
-constexpr float kLog2e = 1.4426950408889634f;
 
 struct DecParams {
   const uint16_t* q;          // [B][Hq][D]
@@ -395,36 +387,10 @@ __global__ __launch_bounds__(64 * (kCascade ? kCascadeWaves : kDecodeWaves)) voi
 // with eight per CU and two pieces per range, 355 with four and four, 486 as
 // contiguous non-temporal ranges (one 12-wave work-group per sequence and KV
 // head: 330).
-constexpr int kRangeGroupsPerCu128 = 3;
-constexpr int kRangeGroupsPerCu64 = 4;
 constexpr int kAlignedGroupsPerCu = 8;
 constexpr int kAlignedPieces = 2;
-constexpr int kUnitKeys = kChunk;
-constexpr int kUnitBlocks = kUnitKeys / kBlock;
 constexpr int kProbeBlock = 31;
 constexpr int kProbeTable = 2 * kRangeMaxBatch;
-// word 3 of a raw buffer descriptor (32-bit data format, no swizzle), and the
-// cache policy bit of a non-temporal buffer load
-constexpr int kRawBufferWord3 = 0x00020000;
-constexpr int kNonTemporal = 2;
-
-__device__ __forceinline__ int units_of(int len) { return (max(len, 0) + kUnitKeys - 1) / kUnitKeys; }
-
-// inclusive prefix sum over the 64 lanes (DPP: shifts within rows of 16, then
-// row 15 and row 31 broadcasts; lanes without a source add 0)
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31
-  return x;
-}
-__device__ __forceinline__ int wave_total(int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
-
-__device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
-
 // units of sequence s (a lane's), 0 past the batch
 __device__ __forceinline__ int units_at(const DecParams& p, int s) {
   return s < p.batch ? units_of(p.seq_lens[s]) : 0;
@@ -471,7 +437,6 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
   constexpr int DT = D / 16;
   constexpr int kRowChunks = D / 8;
   constexpr int kVLoads = kChunk * kRowChunks / 64;
-  constexpr int kTileBytes = kBlock * D * 2;           // one (block, head)
   __shared__ union {
     uint16_t v[kChunk * vStride];
     int probe[kProbeTable];
@@ -482,7 +447,6 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
   const int qd = lane >> 4;
   const int g = blockIdx.x % p.num_kv_heads;
   const int w = blockIdx.x / p.num_kv_heads;
-  typedef const __attribute__((address_space(4))) int32_t* ScalarInts;
   const ScalarInts lens_c = (ScalarInts)p.seq_lens;
 
   // ---- the plan
@@ -597,29 +561,12 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
 
   bf16x8 kreg[2][DC];
   bf16x8 vreg[kVLoads];
-  // K fragments (A operand) and V rows of the blocks id0, id1, through buffer
-  // descriptors over the (block, head) tiles (the per-lane offsets are the
-  // same for every tile).  Where each block is read once V is loaded
-  // non-temporally, so that half the stream leaves the last-level cache alone
-  const int k_off = 2 * (j * D + 8 * qd);
-  const int v_off = 16 * lane;
+  // K fragments and V rows of the blocks id0, id1.  Where each block is read
+  // once V is loaded non-temporally, so that half the stream leaves the
+  // last-level cache alone
   auto load_chunk = [&](int id0, int id1, auto tag) {
-    constexpr int kVPolicy = decltype(tag)::value ? 0 : kNonTemporal;
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      const size_t at = (size_t)(mt ? id1 : id0) * slot_elems;
-      const __amdgpu_buffer_rsrc_t krs =
-          __builtin_amdgcn_make_buffer_rsrc((void*)(kbase + at), (short)0, kTileBytes, kRawBufferWord3);
-      const __amdgpu_buffer_rsrc_t vrs =
-          __builtin_amdgcn_make_buffer_rsrc((void*)(vbase + at), (short)0, kTileBytes, kRawBufferWord3);
-#pragma unroll
-      for (int dc = 0; dc < DC; ++dc)
-        kreg[mt][dc] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(krs, k_off + 64 * dc, 0, 0));
-#pragma unroll
-      for (int v = 0; v < kVLoads / 2; ++v)
-        vreg[mt * (kVLoads / 2) + v] =
-            __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vrs, v_off + 1024 * v, 0, kVPolicy));
-    }
+    load_chunk_tiles<D, decltype(tag)::value ? 0 : kNonTemporal>(kbase, vbase, (size_t)id0 * slot_elems,
+                                                                 (size_t)id1 * slot_elems, lane, kreg, vreg);
   };
   // block ids of a cursor's unit; past the sequence's end its last block again
   // (its keys there are masked, its V rows zeroed)
@@ -772,7 +719,7 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
 // their loads are in flight together, and the teams' results meet in LDS.
 // The launch is one chain of memory latencies (lengths and plan, pieces,
 // output), so what counts is that there are few of them.
-constexpr int kMergeStep = 8;
+constexpr int kMergeStep = 4;
 constexpr int kMergeThreads = 512;     // kMaxGroup * 128 / 4
 template <int D>
 __global__ __launch_bounds__(kMergeThreads) void decode_ranges_merge_kernel(DecParams p) {
@@ -817,8 +764,10 @@ __global__ __launch_bounds__(kMergeThreads) void decode_ranges_merge_kernel(DecP
       f32x4 o[kMergeStep];
 #pragma unroll
       for (int x = 0; x < kMergeStep; ++x) {
-        // past the last piece: the last one again, with weight 0
-        const size_t at = base + (size_t)min(i + x * teams, n - 1) * p.group;
+        ml[x] = make_float2(-INFINITY, 0.f);
+        o[x] = f32x4{};
+        if (i + x * teams >= n) continue;
+        const size_t at = base + (size_t)(i + x * teams) * p.group;
         ml[x] = *reinterpret_cast<const float2*>(p.ws_ml + 2 * at);
         o[x] = *reinterpret_cast<const f32x4*>(p.ws_o + at * D + d);
       }
@@ -831,7 +780,7 @@ __global__ __launch_bounds__(kMergeThreads) void decode_ranges_merge_kernel(DecP
       den *= alpha;
 #pragma unroll
       for (int x = 0; x < kMergeStep; ++x) {
-        const float wt = i + x * teams < n ? __builtin_amdgcn_exp2f((ml[x].x - mx) * c) : 0.f;
+        const float wt = __builtin_amdgcn_exp2f((ml[x].x - mx) * c);      // 0 past the last piece
         acc += wt * o[x];
         den += wt * ml[x].y;
       }
