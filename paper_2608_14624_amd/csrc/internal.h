@@ -50,6 +50,8 @@ struct AttnGeometry {
   long long grid;     // work-groups launched
   long long pp_grid;  // ping-pong work-groups; the rest of the grid (ping-pong
                       // launches only) runs the half tiles of the last round
+                      // (of a batch of equal suffixes: in a ragged one the
+                      // kernel draws the line from the lengths)
   int parts;          // key parts per split tile (1: none; then grid = tiles)
   long long split_tiles;  // split launches: tiles per key part
 };

@@ -52,11 +52,12 @@
 // w and w + 4 own the same rows, waves 0-3 take the first half of the key
 // steps and waves 4-7 the second, each half with its own LDS ring, and at
 // the end the two waves of a pair exchange half of their O through LDS and
-// each merges and stores the other half with the log-sum-exp weights.  A ping-pong launch whose last round
-// would be at most half full runs that round's tiles the same way, as two
-// 128-row halves each, so it occupies every CU.  Launches that leave half
-// the CUs idle even so can take a tile's keys in parts on more work-groups,
-// whose partial results a merge kernel combines (the workspace call).
+// each merges and stores the other half with the log-sum-exp weights.  A
+// ping-pong launch whose last round would be at most half full runs that
+// round's tiles the same way, as two 128-row halves each, so it occupies
+// every CU.  Launches that leave half the CUs idle even so can take a tile's
+// keys in parts on more work-groups, whose partial results a merge kernel
+// combines (the workspace call).
 //
 // Stacked mode (the shared-prefix half of cascade attention): the query rows
 // of a work-group are any 128 (sequence, query head) pairs of one group of
@@ -67,6 +68,7 @@
 // own keys) and the log-sum-exp merge run in the decode kernel.  This kernel
 // stages K and V through registers into a double-buffered LDS tile.
 #include "internal.h"
+#include "wave_ops.h"
 
 #include <math.h>
 
@@ -110,10 +112,11 @@ struct Params {
   int token_tiles;
   int head_tiles;
   float scale_log2;   // scale * log2(e)
-  // ping-pong launches: work-groups below pp_grid take ping-pong tiles; the
-  // rest take the two 128-row halves of the tiles pp_grid, pp_grid + 1, ...
-  // (span = the ping-pong tile's tokens)
-  long long pp_grid;
+  // ping-pong launches
+  int cus;            // compute units (a round of tiles)
+  int even;           // tiles are numbered over max_q_len for every invocation:
+  long long pp_grid;  // work-groups from pp_grid on take halves of the last
+                      // round's tiles
   // shared_prefix_partials_kernel only (ws_o / ws_ml: also the key parts)
   const int32_t* cu_groups;     // [num_groups + 1] sequence range of each group
   const int32_t* shared_lens;   // [num_groups] shared prefix tokens (multiple of 16)
@@ -213,6 +216,123 @@ __device__ __forceinline__ float pair_sum(float x) {
 }
 
 constexpr int kRowsPerWG = kNQ * kWaves;
+
+// A tile of a ping-pong launch.
+struct TileAt {
+  int g;            // KV head
+  int head_tile;
+  int r;            // invocation, its first query row, suffix and prefix lengths
+  int q0, S, P;
+  int token_tile;
+  int half;         // -1: the whole tile, else one of its 128-row halves
+};
+
+// The tile of ping-pong work-group wg in a batch of equal suffixes (or of more
+// than kPlanMaxBatch invocations, some of whose tiles are empty): KV head
+// fastest, then head tiles, then token tiles from the last to the first, then
+// invocations.  kHalves: the work-groups from pp_grid on take the two halves
+// of the tiles pp_grid, pp_grid + 1, ..., num_kv_heads work-groups apart.
+template <bool kHalves>
+__device__ __forceinline__ bool even_tile(const Params& p, int wg, TileAt& t) {
+  int tile = wg;
+  t.half = -1;
+  if (kHalves && wg >= p.pp_grid) {
+    const int j = wg - (int)p.pp_grid;
+    const int pair = j / p.num_kv_heads;
+    t.half = pair & 1;
+    tile = (int)p.pp_grid + (pair >> 1) * p.num_kv_heads + j % p.num_kv_heads;
+  }
+  const int tiles_per_kv = p.head_tiles / p.num_kv_heads;
+  t.g = tile % p.num_kv_heads;
+  const int sub = tile / p.num_kv_heads;
+  t.head_tile = t.g * tiles_per_kv + sub % tiles_per_kv;
+  const int rest = sub / tiles_per_kv;
+  t.r = rest / p.token_tiles;
+  t.token_tile = p.token_tiles - 1 - rest % p.token_tiles;
+  t.q0 = p.cu_q_lens[t.r];
+  t.S = p.cu_q_lens[t.r + 1] - t.q0;
+  if (t.token_tile * p.span >= t.S) return false;
+  t.P = p.prefix_lens[t.r];
+  return true;
+}
+
+// The same in any other batch; false: no tile is left for the work-group.
+//
+// The tiles are those of the invocations' own lengths, in the same order,
+// found from cu_q_lens by every wave, a lane per invocation.  Numbered over
+// the longest invocation's token tiles for every invocation instead, a ragged
+// batch launched work-groups in between that found nothing to do (each held a
+// CU for its start: 8888 of 15104 for 32 invocations of 586-3740 tokens), and
+// a last round that the host could not foresee stayed uneven.  Now the idle
+// ones come last, and (kHalves) a last round at most half full runs as split
+// halves if the grid has work-groups for them (whose pairs must stay
+// num_kv_heads work-groups apart, so the rounds must hold whole groups of KV
+// heads).  us a call, before -> after: 7 invocations of 396-820 tokens on
+// 1500-2500 cached, 32 / 8 heads of 64, 132 -> 114; 32 of 256-2048 tokens, 4 / 1
+// heads of 128, 258 -> 225, and a quarter of them misses, 32 / 8 heads, 1569 ->
+// 1548; 64 of 20-1500 2928 -> 2872.
+// At head_dim 64 the code of the halves costs the ping-pong loop registers (33
+// spilled against 21): from kRoundsWithoutHalves rounds of the bound on, a ragged
+// launch goes without them (32 invocations of 586-3740 tokens: 1097 us with them,
+// and on another box 991 without, 1000 numbered over the longest).
+enum class PPMode { kEven, kHalves, kRagged };
+constexpr int kRoundsWithoutHalves = 8;
+// Past this many invocations every work-group would read too many lengths (300
+// of 20-100 tokens: 460 us numbered over the longest, 477 found).
+constexpr int kPlanMaxBatch = 256;
+template <bool kHalves>
+__device__ __forceinline__ bool ragged_tile(const Params& p, int wg, int lane, TileAt& t) {
+  const int tiles_per_kv = p.head_tiles / p.num_kv_heads;
+  // a lane's invocation: its first row, end and prefix, its tiles
+  int q0, q1, prefix;
+  auto lane_tiles = [&](int r) {
+    q0 = q1 = prefix = 0;
+    if (r < p.batch) {
+      q0 = p.cu_q_lens[r];
+      q1 = p.cu_q_lens[r + 1];
+      prefix = p.prefix_lens[r];
+    }
+    return ceil_div(q1 - q0, p.span) * tiles_per_kv;
+  };
+  int subs = 0;
+  for (int b = 64; b < p.batch; b += 64) subs += __builtin_amdgcn_readlane(wave_scan(lane_tiles(b + lane)), 63);
+  int base = 0, before = 0;            // first of the 64 invocations in the lanes, tiles before them
+  int n = lane_tiles(lane);
+  int incl = wave_scan(n);
+  subs += __builtin_amdgcn_readlane(incl, 63);
+  const int total = subs * p.num_kv_heads;
+  const int tail = total % p.cus;
+  const bool halves = kHalves && tail <= p.cus / 2 && p.cus % p.num_kv_heads == 0 && total + tail <= (int)gridDim.x;
+  const int whole = halves ? total - tail : total;
+  int tile = wg;
+  t.half = -1;
+  if (wg >= whole) {
+    const int j = wg - whole;
+    if (!halves || j >= 2 * tail) return false;
+    const int pair = j / p.num_kv_heads;
+    t.half = pair & 1;
+    tile = whole + (pair >> 1) * p.num_kv_heads + j % p.num_kv_heads;
+  }
+  t.g = tile % p.num_kv_heads;
+  const int sub = tile / p.num_kv_heads;
+  unsigned long long past;
+  while ((past = __builtin_amdgcn_ballot_w64(before + incl > sub)) == 0) {
+    before += __builtin_amdgcn_readlane(incl, 63);
+    base += 64;
+    n = lane_tiles(base + lane);
+    incl = wave_scan(n);
+  }
+  const int l = __builtin_ctzll(past);
+  const int tiles = __builtin_amdgcn_readlane(n, l);
+  const int in_r = sub - (before + __builtin_amdgcn_readlane(incl, l) - tiles);
+  t.r = base + l;
+  t.q0 = __builtin_amdgcn_readlane(q0, l);
+  t.S = __builtin_amdgcn_readlane(q1, l) - t.q0;
+  t.P = __builtin_amdgcn_readlane(prefix, l);
+  t.head_tile = t.g * tiles_per_kv + in_r % tiles_per_kv;
+  t.token_tile = tiles / tiles_per_kv - 1 - in_r / tiles_per_kv;
+  return true;
+}
 
 // One 128-row tile of stacked rows against one chunk of a group's shared
 // prefix: four waves of 32 rows, K and V staged through two register stages
@@ -508,9 +628,9 @@ __global__ __launch_bounds__(kThreads) void shared_prefix_partials_kernel(Params
 // the ping-pong kernel (logits, mask, lazy rescale, exp2, bf16 P, row sums
 // over the same bf16 values, PV), in the same order.
 template <int D, bool kTailTile, bool kPartial = false>
-__device__ __forceinline__ void ppd_split_tile(const Params& p, const int wg, uint16_t* k0, uint16_t* k1,
-                                               uint16_t* k2, uint16_t* k3, uint16_t* v0, uint16_t* v1,
-                                               uint16_t* v2, uint16_t* v3) {
+__device__ __forceinline__ void ppd_split_tile(const Params& p, const int wg, const TileAt& at, uint16_t* k0,
+                                               uint16_t* k1, uint16_t* k2, uint16_t* k3, uint16_t* v0,
+                                               uint16_t* v1, uint16_t* v2, uint16_t* v3) {
   constexpr int KS = D / 16;     // MFMA k-steps over the head dim
   constexpr int DT = D / 32;     // 32-wide output tiles over the head dim
   using DL = DirectLayout<D>;
@@ -527,34 +647,39 @@ __device__ __forceinline__ void ppd_split_tile(const Params& p, const int wg, ui
   // ---- work tile (the order of the ping-pong kernel, with 128-row tiles);
   // the halves of a ping-pong tile are num_kv_heads work-groups apart, so
   // both run on the XCD that holds their KV head
-  const int tiles_per_kv = p.head_tiles / p.num_kv_heads;
-  int tile = wg;
   int sub_half = 0;
   int span = p.span;
   int part = 0;
-  if constexpr (kPartial) {
-    part = wg / p.split_tiles;
-    tile = wg - part * p.split_tiles;
-  }
+  int g, head_tile, r, token_tile, q0, S, P;
   if constexpr (kTailTile) {
-    const long long jt = wg - p.pp_grid;
-    const int kvh = (int)(jt % p.num_kv_heads);
-    const long long rj = jt / p.num_kv_heads;
-    sub_half = (int)(rj & 1);
-    tile = (int)(p.pp_grid + (rj >> 1) * p.num_kv_heads + kvh);
+    g = at.g;
+    head_tile = at.head_tile;
+    r = at.r;
+    q0 = at.q0;
+    S = at.S;
+    P = at.P;
+    token_tile = at.token_tile;
+    sub_half = at.half;
     span = p.span / 2;
+  } else {
+    const int tiles_per_kv = p.head_tiles / p.num_kv_heads;
+    int tile = wg;
+    if constexpr (kPartial) {
+      part = wg / p.split_tiles;
+      tile = wg - part * p.split_tiles;
+    }
+    g = tile % p.num_kv_heads;
+    const int sub = tile / p.num_kv_heads;
+    head_tile = g * tiles_per_kv + sub % tiles_per_kv;
+    const int rest = sub / tiles_per_kv;
+    r = rest / p.token_tiles;
+    token_tile = p.token_tiles - 1 - rest % p.token_tiles;
+    q0 = p.cu_q_lens[r];
+    S = p.cu_q_lens[r + 1] - q0;
+    P = p.prefix_lens[r];
   }
-  const int g = tile % p.num_kv_heads;
-  const int sub = tile / p.num_kv_heads;
-  const int head_tile = g * tiles_per_kv + sub % tiles_per_kv;
-  const int rest = sub / tiles_per_kv;
-  const int r = rest / p.token_tiles;
-  const int token_tile = p.token_tiles - 1 - rest % p.token_tiles;
-  const int q0 = p.cu_q_lens[r];
-  const int S = p.cu_q_lens[r + 1] - q0;
   const int t0 = token_tile * p.span + sub_half * span;
   if (t0 >= S) return;
-  const int P = p.prefix_lens[r];
   const int L = P + S;
   const int h = head_tile * p.heads_per_wg + wave % p.heads_per_wg;
   const int t = t0 + (wave / p.heads_per_wg) * kNQ + qi;   // this lane's suffix row
@@ -859,13 +984,11 @@ __device__ __forceinline__ void ppd_split_tile(const Params& p, const int wg, ui
 
 // The ping-pong kernel (D = 128 and 64).  K and V go straight from HBM into
 // LDS, with no round trip through registers, and the loads of a step have
-// two iterations to land in a three-deep ring of K and V buffers.  kTail:
-// the work-groups from pp_grid on take the 128-row halves of the tiles of
-// the launch's last round (split tiles).
+// two iterations to land in a three-deep ring of K and V buffers.
 // At head_dim 64 the kernel holds at most 128 VGPRs (at least four waves per
-// SIMD) and 50,688 bytes of LDS (67,584 with the tail's two more buffers),
+// SIMD) and 50,688 bytes of LDS (67,584 with the halves' two more buffers),
 // so two work-groups share a CU.
-template <int D, bool kTail>
+template <int D, PPMode kMode>
 __global__ __launch_bounds__(kPPThreads, D == 64 ? 4 : 2) void prefill_paged_attn_ppd_kernel(Params p) {
   using DL = DirectLayout<D>;
   // K and V of three steps, each in its own array so that the compiler can
@@ -873,12 +996,18 @@ __global__ __launch_bounds__(kPPThreads, D == 64 ? 4 : 2) void prefill_paged_att
   constexpr int kBuf = (kBN / DL::kRows) * DL::kGrp;
   __shared__ __attribute__((aligned(16))) uint16_t k0[kBuf], k1[kBuf], k2[kBuf];
   __shared__ __attribute__((aligned(16))) uint16_t v0[kBuf], v1[kBuf], v2[kBuf];
-  const int wg = blockIdx.x;
-  if constexpr (kTail) {
-    if (wg >= p.pp_grid) {
-      // the tail's two-deep rings take two more buffers
+  TileAt at;
+  if constexpr (kMode == PPMode::kEven) {
+    if (!even_tile<false>(p, blockIdx.x, at)) return;
+  } else if constexpr (kMode == PPMode::kRagged) {
+    if (!ragged_tile<false>(p, blockIdx.x, threadIdx.x & 63, at)) return;
+  } else {
+    if (p.even ? !even_tile<true>(p, blockIdx.x, at) : !ragged_tile<true>(p, blockIdx.x, threadIdx.x & 63, at))
+      return;
+    if (at.half >= 0) {
+      // the halves' two-deep rings take two more buffers
       __shared__ __attribute__((aligned(16))) uint16_t k3[kBuf], v3[kBuf];
-      ppd_split_tile<D, true>(p, wg, k0, k1, k2, k3, v0, v1, v2, v3);
+      ppd_split_tile<D, true>(p, blockIdx.x, at, k0, k1, k2, k3, v0, v1, v2, v3);
       return;
     }
   }
@@ -894,20 +1023,10 @@ __global__ __launch_bounds__(kPPThreads, D == 64 ? 4 : 2) void prefill_paged_att
   // two waves of a SIMD belong to different groups
   const bool group_b = __builtin_amdgcn_readfirstlane(wave) >= 4;
 
-  // ---- work tile: KV head fastest, then head tiles, then token tiles from
-  // the last to the first, then invocations
-  const int tiles_per_kv = p.head_tiles / p.num_kv_heads;
-  const int g = wg % p.num_kv_heads;
-  const int sub = wg / p.num_kv_heads;
-  const int head_tile = g * tiles_per_kv + sub % tiles_per_kv;
-  const int rest = sub / tiles_per_kv;
-  const int r = rest / p.token_tiles;
-  const int token_tile = p.token_tiles - 1 - rest % p.token_tiles;
-  const int q0 = p.cu_q_lens[r];
-  const int S = p.cu_q_lens[r + 1] - q0;
+  // ---- work tile
+  const int g = at.g, head_tile = at.head_tile, r = at.r, token_tile = at.token_tile;
+  const int q0 = at.q0, S = at.S, P = at.P;
   const int t0 = token_tile * p.span;
-  if (t0 >= S) return;
-  const int P = p.prefix_lens[r];
   const int L = P + S;
   const int h = head_tile * p.heads_per_wg + wave % p.heads_per_wg;
   const int t = t0 + (wave / p.heads_per_wg) * kNQ + qi;   // this lane's suffix row
@@ -1213,7 +1332,7 @@ __global__ __launch_bounds__(kPPThreads, D == 64 ? 4 : 2) void prefill_paged_att
   constexpr int kBuf = (kBN / DL::kRows) * DL::kGrp;
   __shared__ __attribute__((aligned(16))) uint16_t k0[kBuf], k1[kBuf], k2[kBuf], k3[kBuf];
   __shared__ __attribute__((aligned(16))) uint16_t v0[kBuf], v1[kBuf], v2[kBuf], v3[kBuf];
-  ppd_split_tile<D, false, kPartial>(p, blockIdx.x, k0, k1, k2, k3, v0, v1, v2, v3);
+  ppd_split_tile<D, false, kPartial>(p, blockIdx.x, TileAt{}, k0, k1, k2, k3, v0, v1, v2, v3);
 }
 
 // The output of a split launch with key parts: each (token, head) row
@@ -1330,7 +1449,8 @@ AttnGeometry attn_geometry(int batch, int max_q_len, int max_kv_len, int num_q_h
   }
   // a last round at most half full runs as split half tiles (whose pairs
   // must stay num_kv_heads work-groups apart, so the rounds must hold whole
-  // groups of KV heads)
+  // groups of KV heads); in a ragged batch the kernel sees for itself, within
+  // this grid
   const long long tail = tiles % kCUs;
   if (tiles > kCUs && tail <= kCUs / 2 && kCUs % num_kv_heads == 0) {
     geo.pp_grid = tiles - tail;
@@ -1360,6 +1480,8 @@ hipError_t launch_prefill_paged_attn(const AttnLaunch& a, hipStream_t stream) {
   p.token_tiles = geo.token_tiles;
   p.head_tiles = geo.head_tiles;
   p.scale_log2 = a.scale * kLog2e;
+  p.cus = a.cus;
+  p.even = (long long)a.batch * a.max_q_len == a.total_q || a.batch > kPlanMaxBatch;
   p.pp_grid = geo.pp_grid;
   p.parts = geo.parts;
   p.split_tiles = (int)geo.split_tiles;
@@ -1388,17 +1510,19 @@ hipError_t launch_prefill_paged_attn(const AttnLaunch& a, hipStream_t stream) {
     return hipGetLastError();
   }
   if (geo.waves == kPPWaves) {
-    const bool tail = geo.grid > geo.pp_grid;
+    const bool halves = geo.grid > geo.pp_grid;
     if (a.head_dim == 128) {
-      if (tail) {
-        hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<128, true>), grid, dim3(kPPThreads), 0, stream, p);
+      if (p.even && !halves) {
+        hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<128, PPMode::kEven>), grid, dim3(kPPThreads), 0, stream, p);
       } else {
-        hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<128, false>), grid, dim3(kPPThreads), 0, stream, p);
+        hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<128, PPMode::kHalves>), grid, dim3(kPPThreads), 0, stream, p);
       }
-    } else if (tail) {
-      hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<64, true>), grid, dim3(kPPThreads), 0, stream, p);
+    } else if (p.even && !halves) {
+      hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<64, PPMode::kEven>), grid, dim3(kPPThreads), 0, stream, p);
+    } else if (p.even || geo.grid < (long long)kRoundsWithoutHalves * a.cus) {
+      hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<64, PPMode::kHalves>), grid, dim3(kPPThreads), 0, stream, p);
     } else {
-      hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<64, false>), grid, dim3(kPPThreads), 0, stream, p);
+      hipLaunchKernelGGL((prefill_paged_attn_ppd_kernel<64, PPMode::kRagged>), grid, dim3(kPPThreads), 0, stream, p);
     }
   } else if (a.head_dim == 128) {
     // fewer than one ping-pong work-group per CU: 128-row tiles, each run
