@@ -154,8 +154,16 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# handle of a device's current stream: the raw handle where this torch offers
+# it (0.1 us), else through a Stream object (1.5 us)
+_current_handle = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _stream_handle(stream, device):
     if stream is None:
+        if device.index is not None:
+            return _current_handle(device.index)
         stream = torch.cuda.current_stream(device)
     if isinstance(stream, int):
         return stream
@@ -203,6 +211,21 @@ def _require(cond, msg):
         raise CacheScoutError(CS_ERR_INVALID_ARG, msg)
 
 
+_BF16, _I32 = torch.bfloat16, torch.int32
+
+
+def _require_tensors(dev, index, *tensors):
+    """Each (name, tensor, dtype) contiguous, of its dtype and on the GPU
+    ``dev`` (``index``).  The messages are only made for a tensor that is not:
+    made for every tensor of every call they were most of a small call's
+    host time."""
+    for name, t, dt in tensors:
+        if t.get_device() != index or t.dtype != dt or not t.is_contiguous() or not t.is_cuda:
+            _require(t.device == dev and t.is_cuda, f"{name} must be on {dev}")
+            _require(t.dtype == dt, f"{name} must be {dt}")
+            _require(t.is_contiguous(), f"{name} must be contiguous")
+
+
 ATTN_SPLIT, ATTN_PING_PONG = 0, 1
 
 
@@ -243,14 +266,10 @@ def _prefill_args(q, k_pool, v_pool, block_tables, prefix_lens, cu_q_lens, out, 
     """Validate a prefill attention call's tensors; the C arguments up to the
     scale, the output pointer and the device."""
     dev = q.device
-    for name, t, dt in (("q", q, torch.bfloat16), ("k_pool", k_pool, torch.bfloat16),
-                        ("v_pool", v_pool, torch.bfloat16), ("out", out, torch.bfloat16),
-                        ("block_tables", block_tables, torch.int32),
-                        ("prefix_lens", prefix_lens, torch.int32),
-                        ("cu_q_lens", cu_q_lens, torch.int32)):
-        _require(t.device == dev and t.is_cuda, f"{name} must be on {dev}")
-        _require(t.dtype == dt, f"{name} must be {dt}")
-        _require(t.is_contiguous(), f"{name} must be contiguous")
+    _require_tensors(dev, q.get_device(), ("q", q, _BF16), ("k_pool", k_pool, _BF16),
+                     ("v_pool", v_pool, _BF16), ("out", out, _BF16),
+                     ("block_tables", block_tables, _I32), ("prefix_lens", prefix_lens, _I32),
+                     ("cu_q_lens", cu_q_lens, _I32))
     _require(q.dim() == 3 and out.shape == q.shape, "q and out must be [total_q, Hq, D]")
     _require(k_pool.dim() == 4 and v_pool.shape == k_pool.shape,
              "pools must be [num_blocks, Hkv, block_size, D]")
@@ -267,9 +286,10 @@ def _prefill_args(q, k_pool, v_pool, block_tables, prefix_lens, cu_q_lens, out, 
     return args, _ptr(out), dev
 
 
-def _resolve_workspace(workspace, args, dev):
+def _resolve_workspace(workspace, args, dev, stream=None):
     """None: the call without a workspace.  "auto": a new uint8 GPU tensor of
-    the size the call needs (None if it needs none).  A tensor: used as is."""
+    the size the call needs (None if it needs none), for work on ``stream``.
+    A tensor: used as is."""
     if workspace is None or (isinstance(workspace, str) and workspace == "auto"):
         if workspace is None:
             return None
@@ -279,7 +299,7 @@ def _resolve_workspace(workspace, args, dev):
         _require(need >= 0, "no workspace size for these arguments")
         if need == 0:
             return None
-        return torch.empty(need, dtype=torch.uint8, device=dev)
+        return _scratch(need, stream, dev)
     _require(workspace.is_cuda and workspace.device == dev, f"workspace must be on {dev}")
     return workspace
 
@@ -298,7 +318,7 @@ def cs_prefill_paged_attn(q, k_pool, v_pool, block_tables, prefix_lens, cu_q_len
     """
     args, outp, dev = _prefill_args(q, k_pool, v_pool, block_tables, prefix_lens, cu_q_lens, out,
                                     max_q_len, max_kv_len, scale)
-    ws = _resolve_workspace(workspace, args, dev)
+    ws = _resolve_workspace(workspace, args, dev, stream)
     handle = _stream_handle(stream, dev)
     if workspace is None:
         _check(_lib.cs_prefill_paged_attn(*args, outp, handle))
@@ -385,12 +405,9 @@ def cs_kv_write(k_new, v_new, slot_mapping, k_pool, v_pool, *, stream=None):
     for attention.
     """
     dev = k_pool.device
-    for name, t, dt in (("k_new", k_new, torch.bfloat16), ("v_new", v_new, torch.bfloat16),
-                        ("slot_mapping", slot_mapping, torch.int32),
-                        ("k_pool", k_pool, torch.bfloat16), ("v_pool", v_pool, torch.bfloat16)):
-        _require(t.is_cuda and t.device == dev, f"{name} must be on {dev}")
-        _require(t.dtype == dt, f"{name} must be {dt}")
-        _require(t.is_contiguous(), f"{name} must be contiguous")
+    _require_tensors(dev, k_pool.get_device(), ("k_new", k_new, _BF16), ("v_new", v_new, _BF16),
+                     ("slot_mapping", slot_mapping, _I32), ("k_pool", k_pool, _BF16),
+                     ("v_pool", v_pool, _BF16))
     _require(k_new.shape == v_new.shape and k_new.dim() == 3, "k_new/v_new must be [T, Hkv, D]")
     _require(k_pool.shape == v_pool.shape, "pools must match")
     num_blocks, hkv, bs, d = k_pool.shape
@@ -460,13 +477,9 @@ def cs_paged_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, out, *, max_
     caching allocator's pool of the launch's stream (the C call itself
     allocates nothing)."""
     dev = q.device
-    for name, t, dt in (("q", q, torch.bfloat16), ("k_pool", k_pool, torch.bfloat16),
-                        ("v_pool", v_pool, torch.bfloat16), ("out", out, torch.bfloat16),
-                        ("block_tables", block_tables, torch.int32),
-                        ("seq_lens", seq_lens, torch.int32)):
-        _require(t.is_cuda and t.device == dev, f"{name} must be on {dev}")
-        _require(t.dtype == dt, f"{name} must be {dt}")
-        _require(t.is_contiguous(), f"{name} must be contiguous")
+    _require_tensors(dev, q.get_device(), ("q", q, _BF16), ("k_pool", k_pool, _BF16),
+                     ("v_pool", v_pool, _BF16), ("out", out, _BF16),
+                     ("block_tables", block_tables, _I32), ("seq_lens", seq_lens, _I32))
     _require(q.dim() == 3 and out.shape == q.shape, "q and out must be [B, Hq, D]")
     _require(k_pool.shape == v_pool.shape and k_pool.dim() == 4, "pools must match")
     batch, hq, d = q.shape
@@ -528,14 +541,10 @@ def cs_cascade_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, cu_groups,
     tensor of at least :func:`cs_cascade_decode_workspace_bytes` bytes, or
     None to allocate one here (the C call itself allocates nothing)."""
     dev = q.device
-    for name, t, dt in (("q", q, torch.bfloat16), ("k_pool", k_pool, torch.bfloat16),
-                        ("v_pool", v_pool, torch.bfloat16), ("out", out, torch.bfloat16),
-                        ("block_tables", block_tables, torch.int32),
-                        ("seq_lens", seq_lens, torch.int32), ("cu_groups", cu_groups, torch.int32),
-                        ("shared_lens", shared_lens, torch.int32)):
-        _require(t.is_cuda and t.device == dev, f"{name} must be on {dev}")
-        _require(t.dtype == dt, f"{name} must be {dt}")
-        _require(t.is_contiguous(), f"{name} must be contiguous")
+    _require_tensors(dev, q.get_device(), ("q", q, _BF16), ("k_pool", k_pool, _BF16),
+                     ("v_pool", v_pool, _BF16), ("out", out, _BF16),
+                     ("block_tables", block_tables, _I32), ("seq_lens", seq_lens, _I32),
+                     ("cu_groups", cu_groups, _I32), ("shared_lens", shared_lens, _I32))
     _require(q.dim() == 3 and out.shape == q.shape, "q and out must be [B, Hq, D]")
     _require(k_pool.shape == v_pool.shape and k_pool.dim() == 4, "pools must match")
     batch, hq, d = q.shape
@@ -547,7 +556,7 @@ def cs_cascade_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, cu_groups,
     _require(cu_groups.numel() == num_groups + 1, "cu_groups must have G + 1 entries")
     need = cs_cascade_decode_workspace_bytes(batch, hq, d, int(max_shared_len), int(max_rest_len))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+        workspace = _scratch(max(need, 16), stream, dev)
     _require(workspace.is_cuda and workspace.device == dev, f"workspace must be on {dev}")
     _check(cs_cascade_decode_attn_raw(
         _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables), _ptr(seq_lens), batch,
@@ -565,14 +574,10 @@ def cs_cascade_decode_attn_noalloc(q, k_pool, v_pool, block_tables, seq_lens, cu
     per-device scratch array (no workspace, nothing allocated; calls on one
     device must not overlap).  Tensors as for :func:`cs_cascade_decode_attn`."""
     dev = q.device
-    for name, t, dt in (("q", q, torch.bfloat16), ("k_pool", k_pool, torch.bfloat16),
-                        ("v_pool", v_pool, torch.bfloat16), ("out", out, torch.bfloat16),
-                        ("block_tables", block_tables, torch.int32),
-                        ("seq_lens", seq_lens, torch.int32), ("cu_groups", cu_groups, torch.int32),
-                        ("shared_lens", shared_lens, torch.int32)):
-        _require(t.is_cuda and t.device == dev, f"{name} must be on {dev}")
-        _require(t.dtype == dt, f"{name} must be {dt}")
-        _require(t.is_contiguous(), f"{name} must be contiguous")
+    _require_tensors(dev, q.get_device(), ("q", q, _BF16), ("k_pool", k_pool, _BF16),
+                     ("v_pool", v_pool, _BF16), ("out", out, _BF16),
+                     ("block_tables", block_tables, _I32), ("seq_lens", seq_lens, _I32),
+                     ("cu_groups", cu_groups, _I32), ("shared_lens", shared_lens, _I32))
     _require(q.dim() == 3 and out.shape == q.shape, "q and out must be [B, Hq, D]")
     _require(k_pool.shape == v_pool.shape and k_pool.dim() == 4, "pools must match")
     batch, hq, d = q.shape
