@@ -87,17 +87,21 @@ def load_traffic(kernel, workload, kernel_hash):
     return entry.get("bytes_per_launch")
 
 
-def attention_kernel_name(batch, max_q_len, num_q_heads, num_kv_heads, head_dim, parts=1):
+def attention_kernel_name(batch, max_q_len, num_q_heads, num_kv_heads, head_dim, parts=1,
+                          total_q=None):
     """Which attention kernel a launch runs (the library's own launch rule,
     asked through cs_prefill_paged_attn_launch_shape; ``parts`` > 1: the
-    workspace call's key parts and their merge)."""
+    workspace call's key parts and their merge; ``total_q``: None for equal
+    suffixes)."""
     from paper_2608_14624_amd import ops
     if parts > 1:
         return (f"prefill_paged_attn_ppd_split_kernel<{head_dim}, true> + "
                 f"prefill_split_merge_kernel<{head_dim}>")
     kernel, _, tail = ops.prefill_launch_shape(batch, max_q_len, num_q_heads, num_kv_heads)
     if kernel == ops.ATTN_PING_PONG:
-        return f"prefill_paged_attn_ppd_kernel<{head_dim}, {'true' if tail else 'false'}>"
+        ragged = total_q is not None and total_q != batch * max_q_len
+        mode = "kHalves" if tail else "kRagged or kHalves" if ragged else "kEven"
+        return f"prefill_paged_attn_ppd_kernel<{head_dim}, {mode}>"
     return f"prefill_paged_attn_ppd_split_kernel<{head_dim}, false>"
 
 
@@ -459,12 +463,12 @@ def bench_copy(args, dev):
             ops.cs_kv_offload(ids, k_pool, v_pool, host_k, host_v, stream=stream)
         peak, bound, unit_desc = PEAK_PCIE5_X16_GBS, "host_link", f"{n} blocks"
     kernel, sources = {
-        "decode": ("paged_decode_attn_kernel<128, false>",
-                   ("paper_2608_14624_amd/csrc/paged_decode_attn.hip",)),
-        "cascade_decode": ("shared_prefix_partials_kernel<128> + paged_decode_attn_kernel<128, true>"
-                           " + cascade_merge_kernel<128>",
-                           ("paper_2608_14624_amd/csrc/prefill_paged_attn.hip",
-                            "paper_2608_14624_amd/csrc/paged_decode_attn.hip",
+        "decode": ("decode_ranges_kernel<128> + decode_ranges_merge_kernel<128>",
+                   ("paper_2608_14624_amd/csrc/paged_decode_attn.hip",
+                    "paper_2608_14624_amd/csrc/decode_common.h")),
+        "cascade_decode": ("cascade_ranges_kernel<128> + cascade_ranges_merge_kernel<128>",
+                           ("paper_2608_14624_amd/csrc/cascade_ranges.hip",
+                            "paper_2608_14624_amd/csrc/decode_common.h",
                             "paper_2608_14624_amd/csrc/internal.h")),
         "kv_write": ("kv_write_kernel", ("paper_2608_14624_amd/csrc/kv_copy.hip",)),
         "kv_offload": ("kv_offload_kernel", ("paper_2608_14624_amd/csrc/kv_copy.hip",
@@ -878,7 +882,7 @@ def main():
     batches = pipe.batches if pipe is not None else [pipeline.SubBatch(dw, 0, wl.batch)]
     kernel_names = sorted({attention_kernel_name(b.hi - b.lo, b.max_q_len, wl.num_q_heads,
                                                  wl.num_kv_heads, wl.head_dim,
-                                                 key_parts(b, wl, dw.workspace))
+                                                 key_parts(b, wl, dw.workspace), b.q1 - b.q0)
                            for b in batches})
     kernel_name = " + ".join(kernel_names)
     traffic = load_traffic(kernel_name, args.workload, khash)
