@@ -196,7 +196,8 @@ int64_t cs_prefill_paged_attn_workspace_bytes(int32_t batch, int32_t total_q, in
  *                compute units, less than one round); CS_ATTN_PING_PONG:
  *                256-row tiles, where the last *tail_work_groups work-groups
  *                run the tiles of a last round at most half full as split
- *                128-row halves.
+ *                128-row halves (for equal suffixes; a ragged batch's
+ *                kernel draws that line from the lengths, within *grid).
  *   *grid        work-groups of the launch (0 for a no-op call).
  *   *tail_work_groups  0 unless *kernel is CS_ATTN_PING_PONG.
  *
