@@ -450,11 +450,22 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
   const ScalarInts lens_c = (ScalarInts)p.seq_lens;
 
   // ---- the plan
-  int total = 0;
-  for (int s = 0; s < p.batch; s += 64) total += wave_total(units_at(p, s + lane));
+  int total = 0, longest = 0;
+  for (int s = 0; s < p.batch; s += 64) {
+    const int n = units_at(p, s + lane);
+    total += wave_total(n);
+    longest = max(longest, wave_max(n));
+  }
   const bool aligned = p.batch > 1 && shares_blocks(p, lane, sm.probe);
   const int ranges = aligned ? p.aligned_ranges : p.ranges;     // waves that take part
-  const int per = max(1, ceil_div(total, aligned ? kAlignedPieces * ranges : ranges));
+  // With few KV heads there are more waves than the merge has use for: few
+  // sequences in pieces of one unit leave it hundreds of partials each.  Past
+  // 16 pieces of the longest sequence a range has up to 4 units (8 / 1 heads,
+  // one sequence of 7000 keys 27.3 -> 13.9 us, 3 of 2000-6000 23.3 -> 14.6; 8 of
+  // 100-500 9.8 with 1, 11.3 with 4), an aligned piece always 8 (64 sequences
+  // of 4 agents 48 -> 21 us, 16 of 2 agents 90 -> 27).
+  const int shortest = aligned ? 8 : min(4, ceil_div(longest, 16));
+  const int per = max(max(1, shortest), ceil_div(total, aligned ? kAlignedPieces * ranges : ranges));
   if (blockIdx.x == 0 && lane == 0) *p.plan = make_int2(aligned, per);
 
   // the sequence's slots: its pieces are numbered from here
