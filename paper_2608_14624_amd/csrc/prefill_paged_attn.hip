@@ -1481,7 +1481,13 @@ hipError_t launch_prefill_paged_attn(const AttnLaunch& a, hipStream_t stream) {
   p.head_tiles = geo.head_tiles;
   p.scale_log2 = a.scale * kLog2e;
   p.cus = a.cus;
-  p.even = (long long)a.batch * a.max_q_len == a.total_q || a.batch > kPlanMaxBatch;
+  // At head_dim 64 two ping-pong work-groups share a CU, so every tile of up to
+  // two rounds is resident at once: there is no order to gain from, and finding
+  // the tiles costs (6 ragged misses of 1363-2704 tokens, 8 / 2 heads: 60.8 us
+  // in the bound's numbering, 73.2 found on the device).
+  const bool resident = a.head_dim == 64 && geo.waves == kPPWaves &&
+                        (long long)geo.token_tiles * a.batch * geo.head_tiles <= 2LL * a.cus;
+  p.even = (long long)a.batch * a.max_q_len == a.total_q || a.batch > kPlanMaxBatch || resident;
   p.pp_grid = geo.pp_grid;
   p.parts = geo.parts;
   p.split_tiles = (int)geo.split_tiles;
