@@ -193,15 +193,25 @@ def cs_kv_prefetch_raw(host_k, host_v, dst_block_ids, n, k_pool, v_pool, num_blo
                                num_kv_heads, head_dim, block_size, stream)
 
 
+# handles that HIP gives a meaning of their own: the null stream by two names,
+# and a stream that is another one in every host thread
+_NULL_STREAMS, _PER_THREAD_STREAM = (0, 1), 2
+
+
 def _scratch(nbytes, stream, device):
     """A new uint8 GPU tensor for work on ``stream`` (None: the current
     stream).  It comes from the allocator's pool of that very stream, so its
     memory is neither still in use by work on another stream nor given back
-    before the stream has passed the work that uses it."""
+    before the stream has passed the work that uses it.  None for the
+    per-thread stream: one pool would serve the streams of all threads."""
     if stream is None:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
     if isinstance(stream, int):
-        stream = torch.cuda.ExternalStream(stream, device=device)
+        if stream == _PER_THREAD_STREAM:
+            return None
+        # an ExternalStream of handle 0 would be a new stream of torch's pool
+        stream = (torch.cuda.default_stream(device) if stream in _NULL_STREAMS
+                  else torch.cuda.ExternalStream(stream, device=device))
     with torch.cuda.stream(stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
@@ -288,8 +298,8 @@ def _prefill_args(q, k_pool, v_pool, block_tables, prefix_lens, cu_q_lens, out, 
 
 def _resolve_workspace(workspace, args, dev, stream=None):
     """None: the call without a workspace.  "auto": a new uint8 GPU tensor of
-    the size the call needs (None if it needs none), for work on ``stream``.
-    A tensor: used as is."""
+    the size the call needs (None if it needs none, or ``stream`` can have
+    none), for work on ``stream``.  A tensor: used as is."""
     if workspace is None or (isinstance(workspace, str) and workspace == "auto"):
         if workspace is None:
             return None
@@ -320,11 +330,10 @@ def cs_prefill_paged_attn(q, k_pool, v_pool, block_tables, prefix_lens, cu_q_len
                                     max_q_len, max_kv_len, scale)
     ws = _resolve_workspace(workspace, args, dev, stream)
     handle = _stream_handle(stream, dev)
-    if workspace is None:
+    if ws is None:
         _check(_lib.cs_prefill_paged_attn(*args, outp, handle))
     else:
-        _check(_lib.cs_prefill_paged_attn_ws(*args, _ptr(ws),
-                                             0 if ws is None else ws.numel(), outp, handle))
+        _check(_lib.cs_prefill_paged_attn_ws(*args, _ptr(ws), ws.numel(), outp, handle))
 
 
 class PrefillCall:
@@ -475,7 +484,8 @@ def cs_paged_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, out, *, max_
     ``seq_lens`` int32 ``[B]``, pools and block tables as for prefill.  The
     workspace of ``cs_paged_decode_attn_ws`` is allocated here, from the
     caching allocator's pool of the launch's stream (the C call itself
-    allocates nothing)."""
+    allocates nothing; on the per-thread stream, which has no pool of its own,
+    the call without a workspace is made)."""
     dev = q.device
     _require_tensors(dev, q.get_device(), ("q", q, _BF16), ("k_pool", k_pool, _BF16),
                      ("v_pool", v_pool, _BF16), ("out", out, _BF16),
@@ -492,8 +502,8 @@ def cs_paged_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, out, *, max_
             ctypes.c_float(scale))
     need = paged_decode_workspace_bytes(batch, int(max_seq_len), hq, hkv, d)
     handle = _stream_handle(stream, dev)
-    if need > 0:
-        ws = _scratch(need, stream, dev)
+    ws = _scratch(need, stream, dev) if need > 0 else None
+    if ws is not None:
         _check(_lib.cs_paged_decode_attn_ws(*args, _ptr(ws), need, _ptr(out), handle))
     else:
         _check(_lib.cs_paged_decode_attn(*args, _ptr(out), handle))
@@ -557,6 +567,8 @@ def cs_cascade_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, cu_groups,
     need = cs_cascade_decode_workspace_bytes(batch, hq, d, int(max_shared_len), int(max_rest_len))
     if workspace is None:
         workspace = _scratch(max(need, 16), stream, dev)
+    if workspace is None:              # per-thread stream: ordered with the current one by the caller
+        workspace = _scratch(max(need, 16), None, dev)
     _require(workspace.is_cuda and workspace.device == dev, f"workspace must be on {dev}")
     _check(cs_cascade_decode_attn_raw(
         _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(block_tables), _ptr(seq_lens), batch,
