@@ -1344,8 +1344,10 @@ __global__ __launch_bounds__(kPPThreads, D == 64 ? 4 : 2) void prefill_paged_att
 // The loads of kStep parts (2, 4 or 8: the fewest that hold the launch's
 // parts, so that few are read twice) are in flight together, where a loop over
 // single parts waited for each in turn: calls with 4 to 8 parts 23.1 -> 20.9 us
-// (2656 rows of 128), 22.9 -> 20.0 (512 rows), 20.5 -> 18.0 (664 rows); past the
-// last part the last one is read again, with weight 0.
+// (2656 rows of 128), 22.9 -> 20.0 (512 rows), 20.5 -> 18.0 (664 rows).  Past the
+// last part the buffer loads are out of range and give zeros with weight 0 (the
+// last part read again instead, 0 times an infinite O of it was NaN; zeroed by
+// selects 1-2% of a 12-17 us call).
 template <int D, int kStep>
 __global__ __launch_bounds__(kThreads) void prefill_split_merge_kernel(Params p) {
   constexpr int kTpr = D / 4;
@@ -1357,14 +1359,18 @@ __global__ __launch_bounds__(kThreads) void prefill_split_merge_kernel(Params p)
   float mx = -INFINITY;
   float den = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int rows = p.parts * (int)p.part_rows;
+  const __amdgpu_buffer_rsrc_t ml_rs = __builtin_amdgcn_make_buffer_rsrc(p.ws_ml, (short)0, 8 * rows, kRawBufferWord3);
+  const __amdgpu_buffer_rsrc_t o_rs = __builtin_amdgcn_make_buffer_rsrc(p.ws_o, (short)0, 4 * D * rows, kRawBufferWord3);
   for (int q0 = 0; q0 < p.parts; q0 += kStep) {
     float2 ml[kStep];
     float4 o[kStep];
 #pragma unroll
     for (int q = 0; q < kStep; ++q) {
-      const size_t prow = (size_t)min(q0 + q, p.parts - 1) * p.part_rows + row;
-      ml[q] = *reinterpret_cast<const float2*>(p.ws_ml + 2 * prow);
-      o[q] = *reinterpret_cast<const float4*>(p.ws_o + prow * D + d0);
+      const int prow = (q0 + q) * (int)p.part_rows + (int)row;
+      ml[q] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(ml_rs, 8 * prow, 0, 0));
+      if (q0 + q >= p.parts) ml[q].x = -INFINITY;
+      o[q] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(o_rs, 4 * (prow * D + d0), 0, 0));
     }
     float m_new = mx;
 #pragma unroll
@@ -1379,7 +1385,7 @@ __global__ __launch_bounds__(kThreads) void prefill_split_merge_kernel(Params p)
     acc.w *= alpha;
 #pragma unroll
     for (int q = 0; q < kStep; ++q) {
-      const float w = (q0 + q >= p.parts || ml[q].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((ml[q].x - mx) * c);
+      const float w = ml[q].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml[q].x - mx) * c);
       den += w * ml[q].y;
       acc.x += w * o[q].x;
       acc.y += w * o[q].y;

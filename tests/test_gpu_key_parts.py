@@ -108,6 +108,31 @@ def test_key_part_counts_match_oracle(lens, hq, hkv, parts, head_dim):
 
 
 @pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("lens,hq,hkv,parts", [((1900, 1), 8, 2, 7), ((2300, 1), 8, 2, 9)])
+def test_key_parts_keep_an_infinite_value(lens, hq, hkv, parts, head_dim):
+    """An infinite V feature of the last key (in the last part, which the merge
+    reads again where its step passes the parts) is infinite in the output, and
+    the other features are the oracle's."""
+    from paper_2608_14624_amd import ops, pipeline
+    wl = build_workload("kp_inf", 77, [lens[0]], [Invocation(0, lens[1])], num_q_heads=hq,
+                        num_kv_heads=hkv, head_dim=head_dim, num_blocks=1024)
+    print(f"[case] key parts with an infinite value: parts={parts} D={head_dim}", flush=True)
+    assert parts_of(ops, wl) == parts
+    ref = oracle_full(wl)
+    last = sum(lens) - 1
+    wl.v_pool[wl.block_tables[0, last // 16], :, last % 16, 3] = 0x7F80
+    dw = pipeline.DeviceWorkload(wl, workspace="auto")
+    dw.prefetch_all()
+    dw.out.fill_(float("nan"))
+    dw.attention()
+    torch.cuda.synchronize()
+    got = oracle.bf16_bits_to_f64(dw.out_bits())
+    assert (got[:, :, 3] == np.inf).all()
+    rest = np.arange(head_dim) != 3
+    assert np.abs(got[:, :, rest] - ref[:, :, rest]).max() <= MAX_ABS
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
 def test_key_parts_with_peaky_logits(head_dim):
     """Queries scaled up 8x (logits in the tens of log2 units): the parts'
     maxima differ widely, and the merge's log-sum-exp weights must still
