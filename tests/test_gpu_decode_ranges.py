@@ -104,6 +104,63 @@ def test_ranges_match_oracle(name):
     assert np.abs(got - oracle.bf16_bits_to_f64(bits(plain))).max() <= MAX_ABS
 
 
+def both_calls(wl, q, seq_lens):
+    """Outputs (float64) of the call in ranges and of the one without a workspace."""
+    from paper_2608_14624_amd import ops
+    hq, hkv, d, bound = wl.num_q_heads, wl.num_kv_heads, wl.head_dim, int(seq_lens.max())
+    args = (dev(q), dev(wl.k_pool), dev(wl.v_pool), dev(wl.block_tables), dev(seq_lens))
+    assert ops.paged_decode_workspace_bytes(wl.batch, bound, hq, hkv, d) > 0
+    out, plain = (torch.full_like(args[0], float("nan")) for _ in range(2))
+    ops.cs_paged_decode_attn(*args, out, max_seq_len=bound, scale=wl.scale)
+    p = [t.data_ptr() for t in args]
+    assert ops.cs_paged_decode_attn_raw(*p, wl.batch, bound, wl.block_tables.shape[1], wl.num_blocks, hq,
+                                        hkv, d, 16, wl.scale, plain.data_ptr()) == ops.CS_OK
+    torch.cuda.synchronize()
+    return [oracle.bf16_bits_to_f64(bits(t)) for t in (out, plain)]
+
+
+def oracle_rows(wl, q, seq_lens):
+    hq, hkv = wl.num_q_heads, wl.num_kv_heads
+    samples = [(r, h, 0) for r in range(wl.batch) for h in range(hq)]
+    return oracle.prefill_paged_attn_rows(q, wl.k_pool, wl.v_pool, wl.block_tables,
+                                          seq_lens.astype(np.int32) - 1,
+                                          np.arange(wl.batch + 1, dtype=np.int32), hq, hkv, wl.scale,
+                                          samples).reshape(wl.batch, hq, wl.head_dim)
+
+
+@pytest.mark.parametrize("anchors", [None, [1200]])
+@pytest.mark.parametrize("d", [64, 128])
+def test_ranges_are_as_close_as_the_call_without_a_workspace(d, anchors):
+    """Long ranges lose no precision against the 12 partial sums of a sequence in
+    the call without a workspace.  The 2-norm of about 100,000 independent roundings
+    repeats to about 0.2%, so 1% is five times that."""
+    lens = [2000 + (811 * i) % 3000 for i in range(32)]
+    wl = workload(lens, 32, 8, d, anchors)
+    q, seq_lens = decode_view(wl)
+    ref = oracle_rows(wl, q, seq_lens)
+    err, err_plain = (np.linalg.norm(x - ref) / np.linalg.norm(ref) for x in both_calls(wl, q, seq_lens))
+    print(f"[case] precision D={d} anchors={anchors}: ranges {err:.6f}, plain {err_plain:.6f}", flush=True)
+    assert err <= 1.01 * err_plain
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_ranges_with_logits_of_minus_infinity(d):
+    """32 keys whose logits are -inf, at the first unit of a range, inside one
+    and at a sequence's start, weigh nothing."""
+    wl = workload([3000, 700], 4, 4, d)
+    q, seq_lens = decode_view(wl)
+    q[:, :, 0] = 0x3F80                                    # 1.0
+    ref_pool = wl.k_pool.copy()
+    for r, first in ((0, 0), (0, 64), (0, 96), (0, 1024), (1, 160)):
+        for b in (first // 16, first // 16 + 1):
+            wl.k_pool[wl.block_tables[r, b], :, :, 0] = 0xFF80          # -inf
+            ref_pool[wl.block_tables[r, b], :, :, 0] = 0xC8C3           # -399,360: exp of it is 0 as well
+    got = both_calls(wl, q, seq_lens)[0]
+    wl.k_pool = ref_pool
+    assert np.isfinite(got).all()
+    assert np.abs(got - oracle_rows(wl, q, seq_lens)).max() <= MAX_ABS
+
+
 @pytest.mark.parametrize("anchors", [None, [800]])
 def test_ranges_on_another_stream_and_in_a_graph(anchors):
     """The workspace comes from the pool of the launch's stream: calls on two
