@@ -298,7 +298,7 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
   bf16x8 kreg[2][DC];
   bf16x8 vreg[kVLoads];
   auto load_chunk = [&](int id0, int id1) {
-    load_chunk_tiles<D, kNonTemporal>(kbase, vbase, (size_t)id0 * slot_elems, (size_t)id1 * slot_elems, lane, kreg, vreg);
+    load_chunk_tiles<D, kNonTemporal>(kbase, vbase, id0, id1, slot_elems, lane, kreg, vreg);
   };
   // block ids of a cursor's unit; past the list's end its last block again (its
   // keys there are masked, its V rows zeroed)

@@ -74,11 +74,13 @@ __device__ __forceinline__ float quad_sum(float x) {
 }
 
 // K fragments (A operand of the 16x16x32 MFMA) and V rows of one chunk, the
-// (block, head) tiles at elements at0 and at1 of the pools, through buffer
-// descriptors over the tiles: the per-lane offsets are the same for every tile.
+// tiles of blocks id0 and id1 (of the KV head that the pools start at), through
+// buffer descriptors over the tiles: the per-lane offsets are the same for every
+// tile.  The descriptor of a negative block id is empty, so its K and V are 0, as
+// in paged_decode_attn_kernel, and nothing outside the pools is read.
 template <int D, int kVPolicy>
-__device__ __forceinline__ void load_chunk_tiles(const uint16_t* k_pool, const uint16_t* v_pool, size_t at0,
-                                                 size_t at1, int lane, bf16x8 (&kreg)[2][D / 32],
+__device__ __forceinline__ void load_chunk_tiles(const uint16_t* k_pool, const uint16_t* v_pool, int id0, int id1,
+                                                 size_t slot_elems, int lane, bf16x8 (&kreg)[2][D / 32],
                                                  bf16x8 (&vreg)[kChunk * D / 8 / 64]) {
   constexpr int kTileBytes = kBlock * D * 2;
   constexpr int kVPerBlock = kChunk * D / 8 / 64 / 2;
@@ -86,11 +88,13 @@ __device__ __forceinline__ void load_chunk_tiles(const uint16_t* k_pool, const u
   const int v_off = 16 * lane;
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt) {
-    const size_t at = mt ? at1 : at0;
+    const int id = mt ? id1 : id0;
+    const size_t at = (size_t)id * slot_elems;
+    const int bytes = id < 0 ? 0 : kTileBytes;
     const __amdgpu_buffer_rsrc_t krs =
-        __builtin_amdgcn_make_buffer_rsrc((void*)(k_pool + at), (short)0, kTileBytes, kRawBufferWord3);
+        __builtin_amdgcn_make_buffer_rsrc((void*)(k_pool + at), (short)0, bytes, kRawBufferWord3);
     const __amdgpu_buffer_rsrc_t vrs =
-        __builtin_amdgcn_make_buffer_rsrc((void*)(v_pool + at), (short)0, kTileBytes, kRawBufferWord3);
+        __builtin_amdgcn_make_buffer_rsrc((void*)(v_pool + at), (short)0, bytes, kRawBufferWord3);
 #pragma unroll
     for (int dc = 0; dc < D / 32; ++dc)
       kreg[mt][dc] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(krs, k_off + 64 * dc, 0, 0));

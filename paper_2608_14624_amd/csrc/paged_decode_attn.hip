@@ -577,8 +577,7 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
   // once V is loaded non-temporally, so that half the stream leaves the
   // last-level cache alone
   auto load_chunk = [&](int id0, int id1, auto tag) {
-    load_chunk_tiles<D, decltype(tag)::value ? 0 : kNonTemporal>(kbase, vbase, (size_t)id0 * slot_elems,
-                                                                 (size_t)id1 * slot_elems, lane, kreg, vreg);
+    load_chunk_tiles<D, decltype(tag)::value ? 0 : kNonTemporal>(kbase, vbase, id0, id1, slot_elems, lane, kreg, vreg);
   };
   // block ids of a cursor's unit; past the sequence's end its last block again
   // (its keys there are masked, its V rows zeroed)

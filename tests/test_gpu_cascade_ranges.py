@@ -128,3 +128,36 @@ def test_cascade_ranges_match_oracle(name, poison):
     err = np.abs(got - ref)
     print(f"    vs oracle max_abs={err.max():.3e} mean_abs={err.mean():.3e}", flush=True)
     assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+
+
+def test_cascade_ranges_take_a_negative_block_id_as_zeros():
+    """Blocks without a slot, shared and own, count as zero K and V and are not
+    read, as in the launches in chunks and segments."""
+    from paper_2608_14624_amd import ops
+    groups, hq, hkv, d, parts = CASES["agents"]
+    wl, q, seq_lens, cu, shared = build(groups, hq, hkv, d)
+    free = sorted(set(range(wl.num_blocks)) - set(wl.block_tables.flatten().tolist()))[0]
+    zeroed = wl.block_tables.copy()
+    for r, b in ((r, b) for gr in (1, 3) for r in range(cu[gr], cu[gr + 1])
+                 for b in (2, int(shared[gr]) // 16 - 1, int(seq_lens[r] - 1) // 16)):
+        wl.block_tables[r, b] = -3
+        zeroed[r, b] = free
+    rest = max(int(seq_lens[i]) - int(shared[gr]) for gr in range(len(shared)) for i in range(cu[gr], cu[gr + 1]))
+    rest = max(rest, (parts - -(-int(shared.max()) // 1024)) * 1024)
+    bound = max(int(seq_lens.max()), rest)
+    bt = np.concatenate([wl.block_tables, np.full((wl.batch, max(0, -(-bound // 16) - wl.block_tables.shape[1])),
+                                                  -1, np.int32)], 1)
+    max_seqs = max(len(o) for _, o in groups)
+    assert takes_ranges(wl.batch, len(shared), max_seqs, hq, hkv, d, int(shared.max()), rest)
+    args = [dev(x) for x in (q, wl.k_pool, wl.v_pool, bt, seq_lens, cu, shared)]
+    out = torch.full_like(args[0], float("nan"))
+    ops.cs_cascade_decode_attn(*args, out, max_seq_len=bound, max_group_seqs=max_seqs,
+                               max_shared_len=int(shared.max()), max_rest_len=rest, scale=wl.scale)
+    torch.cuda.synchronize()
+    wl.k_pool[free] = wl.v_pool[free] = 0
+    samples = [(r, h, 0) for r in range(wl.batch) for h in range(hq)]
+    ref = oracle.prefill_paged_attn_rows(q, wl.k_pool, wl.v_pool, zeroed, seq_lens - 1,
+                                         np.arange(wl.batch + 1, dtype=np.int32), hq, hkv, wl.scale,
+                                         samples).reshape(wl.batch, hq, d)
+    got = oracle.bf16_bits_to_f64(out.view(torch.int16).cpu().numpy().view(np.uint16))
+    assert np.abs(got - ref).max() <= MAX_ABS

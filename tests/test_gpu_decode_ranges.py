@@ -161,6 +161,27 @@ def test_ranges_with_logits_of_minus_infinity(d):
     assert np.abs(got - oracle_rows(wl, q, seq_lens)).max() <= MAX_ABS
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_ranges_take_a_negative_block_id_as_zeros(d):
+    """Blocks without a slot (a negative id, the one that is probed for sharing among
+    them) count as zero K and V and are not read, as in the call without a
+    workspace."""
+    wl = workload([1500, 700, 2100, 90], 8, 2, d)
+    q, seq_lens = decode_view(wl)
+    free = sorted(set(range(wl.num_blocks)) - set(wl.block_tables.flatten().tolist()))[0]
+    zeroed = wl.block_tables.copy()
+    for r, b in ((0, 0), (0, 31), (0, 93), (1, 31), (1, 32), (2, 64), (3, 5)):
+        wl.block_tables[r, b] = -1 - 7 * r
+        zeroed[r, b] = free
+    got, plain = both_calls(wl, q, seq_lens)
+    wl.block_tables = zeroed
+    wl.k_pool[free] = wl.v_pool[free] = 0
+    ref = oracle_rows(wl, q, seq_lens)
+    assert np.isfinite(got).all() and np.isfinite(plain).all()
+    assert np.abs(plain - ref).max() <= MAX_ABS
+    assert np.abs(got - ref).max() <= MAX_ABS
+
+
 @pytest.mark.parametrize("anchors", [None, [800]])
 def test_ranges_on_another_stream_and_in_a_graph(anchors):
     """The workspace comes from the pool of the launch's stream: calls on two
