@@ -279,18 +279,20 @@ int cs_paged_decode_attn(const void *q, const void *k_pool, const void *v_pool,
  *
  * cs_paged_decode_attn gives every (sequence, KV head) one work-group.  This
  * call counts the batch's keys in units of 32 and deals them to a few one-wave
- * work-groups per compute unit, in equal contiguous ranges, or, where two
- * sequences hold the same pool block at index 31 (a shared anchor), in pieces
- * cut at the same positions of every sequence.  A sequence cut over several
- * ranges leaves fp32 partial results (O relative to its running maximum m,
- * m, and the probability sum l) in the workspace, which a second kernel
- * combines with log-sum-exp weights into the bf16 output.  The plan is made
- * on the device from seq_lens, so a loose max_seq_len costs nothing.  The
- * result equals cs_paged_decode_attn's up to rounding order, and is the same
- * from run to run.  Batches above 1024, calls with max_seq_len up to 128, and at
- * head_dim 64 up to 512 while batch * num_kv_heads <= compute units, ignore the
- * workspace and run exactly as cs_paged_decode_attn; so does a call whose out
- * is not 16-byte aligned.
+ * work-groups per compute unit, in equal contiguous ranges, or, in a long
+ * enough launch with enough sequences on a shared anchor (the same pool block
+ * at index 31), in pieces cut at the same positions of every sequence.  A
+ * sequence cut over several ranges leaves fp32 partial results (O relative to
+ * its running maximum m, m, and the probability sum l) in the workspace, which
+ * a second kernel combines with log-sum-exp weights into the bf16 output.  The
+ * plan is made on the device from seq_lens, so a loose max_seq_len costs
+ * nothing.  The result equals cs_paged_decode_attn's up to rounding order, and
+ * is the same from run to run; where a sequence is cut depends on the whole
+ * batch, so unlike there the low bits of its rows may change with the other
+ * sequences and with its place among them.  Batches above 1024, calls with
+ * max_seq_len up to 128, and at head_dim 64 up to 512 while batch *
+ * num_kv_heads <= compute units, ignore the workspace and run exactly as
+ * cs_paged_decode_attn; so does a call whose out is not 16-byte aligned.
  *
  * Arguments as in cs_paged_decode_attn, plus
  *   workspace        device, 16-byte aligned, caller-owned scratch of at least

@@ -491,7 +491,6 @@ __global__ __launch_bounds__(kMergeThreads) void cascade_ranges_merge_kernel(Cas
   const int n_own = own_units > 0 ? (own_first + own_units - 1) / per - w_own + 1 : 0;
   const float c = p.scale_log2;
   const int elems = p.group * (D / 4);   // threads of a team
-  const int teams = kMergeThreads / elems;
   const int team = threadIdx.x / elems;
   const int idx = threadIdx.x - team * elems;
   const int hj = idx / (D / 4);
@@ -505,6 +504,7 @@ __global__ __launch_bounds__(kMergeThreads) void cascade_ranges_merge_kernel(Cas
   const int shared_row = (group_cb + cb + w_cb) * p.width + rho % p.width;
   const int own_row = own_at + (r + w_own - own_w) * p.group + hj;
   const int n = n_shared + n_own;
+  const int teams = min(kMergeThreads / elems, max(1, ceil_div(n, kMergeStep)));   // as many as have work
   float mx = -INFINITY, den = 0.f;
   f32x4 acc = f32x4{};
   if (team < teams) {

@@ -125,7 +125,7 @@ struct DecodeLaunch {
 };
 
 // A decode launch with a workspace deals the batch's keys to one-wave
-// work-groups, `ranges` per KV head (`aligned_ranges` where sequences share
+// work-groups, `ranges` per KV head (`aligned_ranges` where enough of them share
 // blocks), which leave partial results in `slots` workspace slots per KV head.
 // All 0: one work-group per (sequence, KV head) instead, no workspace.
 struct DecodeGeometry {

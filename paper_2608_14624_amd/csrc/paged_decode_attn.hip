@@ -360,12 +360,12 @@ __global__ __launch_bounds__(64 * (kCascade ? kCascadeWaves : kDecodeWaves)) voi
 // so the host needs no lengths and no tight bound of them.
 //   * Nothing shared: the sequences' units are laid end to end in batch order
 //     and dealt in equal contiguous ranges of ceil(total / ranges) units.
-//   * Sequences that share a prefix (the same pool block at index
-//     kProbeBlock of two block tables): every sequence is cut at the same
-//     positions, multiples of ceil(total / (kAlignedPieces ranges)) units, and
-//     the waves take the first pieces of all sequences, then the second ones, ...,
-//     so that sequences with the same blocks read them at about the same time
-//     and most find them in L2.
+//   * Where enough of the batch shares prefixes (counted by the pool block at
+//     index kProbeBlock of the block tables): every sequence is cut at the same
+//     positions, multiples of ceil(total / (aligned_rounds ranges)) units, and the
+//     waves take the first pieces of all sequences, then the second ones, ..., so
+//     that sequences with the same blocks read them at about the same time and
+//     most find them in L2.
 // A piece of a sequence that is not the whole of it leaves a partial result (O
 // relative to its running max m, the max m and the sum l) in a slot of the
 // workspace, and decode_ranges_merge_kernel combines a sequence's pieces.  The
@@ -384,42 +384,65 @@ __global__ __launch_bounds__(64 * (kCascade ? kCascadeWaves : kDecodeWaves)) voi
 // chunk is half the bytes (three: 5% slower).  K and V both non-temporal is up
 // to 4% faster than V alone, but 17% slower where the pools were written just
 // before (4 GB of them: 875 us against 749; ordinary loads 797).  Sequences that
-// share want ordinary loads and more waves: 128 sequences of 8 agents 317 us
-// with eight per CU and two pieces per range, 355 with four and four, 486 as
-// contiguous non-temporal ranges (one 12-wave work-group per sequence and KV
-// head: 330).
-constexpr int kAlignedGroupsPerCu = 8;
-constexpr int kAlignedPieces = 2;
+// share want ordinary loads and more waves, at head_dim 128 eight per CU with two
+// pieces each (128 sequences of 8 agents 317 us, four and four 355), at 64, where
+// a unit is half the bytes, sixteen with one (256 sequences of 8 agents, 8 / 2
+// heads, 86 us; eight and two 97, one work-group per sequence and KV head 89).
+//
+// For sequences with blocks of their own the aligned pieces are the slower ones
+// (many waves, ordinary loads): 128 of 6000-9000 keys, two of them on one anchor,
+// 32 / 8 heads of 128, 592 us in ranges, 676 in pieces, one work-group each 648.
+// And short launches lose in pieces what the order saves: the pieces' ends do not
+// meet the work of the waves.  Pieces are therefore taken where at least a
+// quarter of the sequences are on a block counted before (kSharingPart), and that
+// share times the units of an equal range is at least kSharedUnits.  us a call,
+// ranges and pieces, at share times units: 4 / 1 heads of 64, 128 sequences of one
+// agent 18.5 and 22.7 (11), 500 of 16 45.3 and 48.3 (29), 256 of 8 61 and 54 (52);
+// 8 / 2 of 64, 128 of one 25.1 and 26.4 (21), 500 of 16 68 and 61 (57), 128 of 64
+// 32 and 38 (11); 32 / 8 of 64, 24 of 3 18.3 and 19.8 (11), 64 of 4 47.8 and 42.2
+// (42); 32 / 8 of 128, 16 of 2 46.9 and 48.4 (31), 64 of 4 75 and 67 (56); of 128
+// sequences of 6000-9000 keys 64 in pairs (a quarter counted: 67) 555 and 532 at
+// 128, 269 and 281 at 64, and 48 in pairs 565 and 568, 273 and 302.
+// Pieces per CU and KV head, and how many of them a wave takes:
+constexpr int kAlignedPiecesPerCu = 16;
+constexpr int aligned_rounds(int head_dim) { return head_dim == 64 ? 1 : 2; }
+constexpr int kSharingPart = 4;
+constexpr int kSharedUnits = 36;
 constexpr int kProbeBlock = 31;
 constexpr int kProbeTable = 2 * kRangeMaxBatch;
-// units of sequence s (a lane's), 0 past the batch
-__device__ __forceinline__ int units_at(const DecParams& p, int s) {
-  return s < p.batch ? units_of(p.seq_lens[s]) : 0;
-}
+constexpr int kPlanRounds = kRangeMaxBatch / 64;
 
-// whether two sequences hold the same pool block at index kProbeBlock: a hash
-// table of the blocks in LDS (one wave; at most half full)
-__device__ __forceinline__ bool shares_blocks(const DecParams& p, int lane, int* table) {
+// How many of the batch's sequences hold the pool block at index kProbeBlock that
+// another one counted before them holds (one wave; ids: the lane's sequences',
+// -1 where there is none): a hash table of the blocks in LDS, at most half full.
+// The count is that of all less the different ones, so it does not depend on the
+// order in which the lanes meet.
+__device__ __forceinline__ int count_sharing(const int (&ids)[kPlanRounds], int batch, int lane, int* table) {
   for (int i = lane; i < kProbeTable; i += 64) table[i] = -1;
   __syncthreads();
-  bool dup = false;
-  for (int s = lane; s < p.batch; s += 64) {
-    if (p.seq_lens[s] <= kProbeBlock * kBlock) continue;
-    const int id = p.block_tables[(size_t)s * p.max_blocks_per_seq + kProbeBlock];
-    unsigned h = ((unsigned)id * 2654435761u) >> 16;
-    for (int tries = 0; tries < kProbeTable; ++tries) {
-      h %= kProbeTable;
-      const int old = atomicCAS(&table[h], -1, id);
-      if (old == -1) break;
-      if (old == id) {
-        dup = true;
-        break;
+  int dups = 0;
+#pragma unroll
+  for (int i = 0; i < kPlanRounds; ++i) {
+    if (64 * i >= batch) break;
+    const int id = ids[i];
+    bool dup = false;
+    if (id >= 0) {
+      unsigned h = ((unsigned)id * 2654435761u) >> 16;
+      for (int tries = 0; tries < kProbeTable; ++tries) {
+        h %= kProbeTable;
+        const int old = atomicCAS(&table[h], -1, id);
+        if (old == -1) break;
+        if (old == id) {
+          dup = true;
+          break;
+        }
+        ++h;
       }
-      ++h;
     }
+    dups += __builtin_popcountll(__builtin_amdgcn_ballot_w64(dup));
   }
   __syncthreads();
-  return __builtin_amdgcn_ballot_w64(dup) != 0;
+  return dups;
 }
 
 // A position in a wave's list of pieces.
@@ -438,8 +461,12 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
   constexpr int DT = D / 16;
   constexpr int kRowChunks = D / 8;
   constexpr int kVLoads = kChunk * kRowChunks / 64;
+  constexpr int kManyUnits = 0xffff;
   __shared__ union {
-    uint16_t v[kChunk * vStride];
+    struct {
+      uint16_t v[kChunk * vStride];
+      uint16_t units[kRangeMaxBatch];    // of every sequence (kManyUnits: that many or more)
+    };
     int probe[kProbeTable];
   } sm;
 
@@ -450,29 +477,60 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
   const int w = blockIdx.x / p.num_kv_heads;
   const ScalarInts lens_c = (ScalarInts)p.seq_lens;
 
-  // ---- the plan
-  int total = 0, longest = 0;
-  for (int s = 0; s < p.batch; s += 64) {
-    const int n = units_at(p, s + lane);
-    total += wave_total(n);
-    longest = max(longest, wave_max(n));
+  // ---- the plan.  All lengths and probed blocks are asked for at once, and the
+  // units then kept in LDS: read from memory again for every piece, a batch of
+  // 256 spent longer on finding its last pieces than on a short piece itself.
+  int n_of[kPlanRounds], ids_probed[kPlanRounds];
+#pragma unroll
+  for (int i = 0; i < kPlanRounds; ++i) {
+    n_of[i] = 0;
+    ids_probed[i] = -1;
+    if (64 * i >= p.batch) continue;
+    const int s = 64 * i + lane;
+    if (s < p.batch) {
+      n_of[i] = p.seq_lens[s];
+      if (p.batch > 1 && p.max_blocks_per_seq > kProbeBlock)
+        ids_probed[i] = p.block_tables[(size_t)s * p.max_blocks_per_seq + kProbeBlock];
+    }
   }
-  const bool aligned = p.batch > 1 && shares_blocks(p, lane, sm.probe);
+  int total = 0, longest = 0;
+#pragma unroll
+  for (int i = 0; i < kPlanRounds; ++i) {
+    if (64 * i >= p.batch) continue;
+    if (n_of[i] <= kProbeBlock * kBlock) ids_probed[i] = -1;      // an entry past its last block
+    n_of[i] = units_of(n_of[i]);
+    total += wave_total(n_of[i]);
+    longest = max(longest, wave_max(n_of[i]));
+  }
+  bool aligned = false;
+  if (p.batch > 1 && total >= kSharedUnits * p.ranges) {
+    const int sharing = count_sharing(ids_probed, p.batch, lane, sm.probe);
+    aligned = kSharingPart * sharing >= p.batch &&
+              (long long)sharing * total >= (long long)kSharedUnits * p.batch * p.ranges;
+  }
+#pragma unroll
+  for (int i = 0; i < kPlanRounds; ++i)
+    if (64 * i < p.batch) sm.units[64 * i + lane] = (uint16_t)min(n_of[i], kManyUnits);
+  __syncthreads();
+  auto units_at = [&](int s) {           // of sequence s (a lane's), 0 past the batch
+    if (s >= p.batch) return 0;
+    const int n = sm.units[s];
+    return n == kManyUnits ? units_of(p.seq_lens[s]) : n;
+  };
   const int ranges = aligned ? p.aligned_ranges : p.ranges;     // waves that take part
   // With few KV heads there are more waves than the merge has use for: few
   // sequences in pieces of one unit leave it hundreds of partials each.  Past
   // 16 pieces of the longest sequence a range has up to 4 units (8 / 1 heads,
   // one sequence of 7000 keys 27.3 -> 13.9 us, 3 of 2000-6000 23.3 -> 14.6; 8 of
-  // 100-500 9.8 with 1, 11.3 with 4), an aligned piece always 8 (64 sequences
-  // of 4 agents 48 -> 21 us, 16 of 2 agents 90 -> 27).
-  const int shortest = aligned ? 8 : min(4, ceil_div(longest, 16));
-  const int per = max(max(1, shortest), ceil_div(total, aligned ? kAlignedPieces * ranges : ranges));
+  // 100-500 9.8 with 1, 11.3 with 4).  Aligned pieces are longer by their rule.
+  const int shortest = min(4, ceil_div(longest, 16));
+  const int per = max(max(1, shortest), ceil_div(total, aligned ? aligned_rounds(D) * ranges : ranges));
   if (blockIdx.x == 0 && lane == 0) *p.plan = make_int2(aligned, per);
 
   // the sequence's slots: its pieces are numbered from here
   auto piece_base = [&](int r) {
     int t = 0;
-    for (int s = 0; s < r; s += 64) t += wave_total(s + lane < r ? ceil_div(units_at(p, s + lane), per) : 0);
+    for (int s = 0; s < r; s += 64) t += wave_total(s + lane < r ? ceil_div(units_at(s + lane), per) : 0);
     return t;
   };
   // aligned pieces in order of (piece, sequence): the wave's are w, w + ranges, ...
@@ -481,7 +539,7 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
     for (;; ++piece) {
       int count = 0;
       for (int s = 0; s < p.batch; s += 64)
-        count += __builtin_popcountll(__builtin_amdgcn_ballot_w64(units_at(p, s + lane) > piece * per));
+        count += __builtin_popcountll(__builtin_amdgcn_ballot_w64(units_at(s + lane) > piece * per));
       if (count == 0) {
         c.valid = false;
         return;
@@ -491,7 +549,7 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
     }
     int before = 0;
     for (int s = 0; s < p.batch; s += 64) {
-      const unsigned long long mask = __builtin_amdgcn_ballot_w64(units_at(p, s + lane) > piece * per);
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(units_at(s + lane) > piece * per);
       const int n = __builtin_popcountll(mask);
       if (rank < before + n) {
         const int mine = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
@@ -528,7 +586,7 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
     if (left > 0) {
       int first = 0;                                    // first unit of sequence ids.r
       for (int s = 0;; s += 64) {
-        const int n = units_at(p, s + lane);
+        const int n = units_at(s + lane);
         const int incl = wave_scan(n);
         const unsigned long long past = __builtin_amdgcn_ballot_w64(first + incl > u);
         if (past != 0) {
@@ -903,8 +961,10 @@ DecodeGeometry decode_geometry(int batch, int max_seq_len, int num_kv_heads, int
   if (head_dim == 64 && max_seq_len <= 512 && (long long)batch * num_kv_heads <= cus) return geo;
   const int groups_per_cu = head_dim == 128 ? kRangeGroupsPerCu128 : kRangeGroupsPerCu64;
   geo.ranges = std::max(1, groups_per_cu * cus / num_kv_heads);
-  geo.aligned_ranges = std::max(1, kAlignedGroupsPerCu * cus / num_kv_heads);
-  geo.slots = std::max(geo.ranges, kAlignedPieces * geo.aligned_ranges) + batch;
+  const int rounds = aligned_rounds(64) * aligned_rounds(128);     // a whole number of waves at both
+  const int pieces = rounds * std::max(1, kAlignedPiecesPerCu / rounds * cus / num_kv_heads);
+  geo.aligned_ranges = pieces / aligned_rounds(head_dim);
+  geo.slots = std::max(geo.ranges, pieces) + batch;
   return geo;
 }
 

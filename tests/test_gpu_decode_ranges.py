@@ -6,8 +6,10 @@ Sizes sit at the edges of the plan: one sequence; lengths around the 32-key
 unit and the 16-token block; many more units than ranges and fewer; sequences
 cut over many ranges beside whole ones; KV head counts that leave the ranges
 uneven; more than 64 sequences (one lane each); a bound far above the lengths;
-and the same for sequences that share their first blocks, which are cut at the
-same positions, with sharing that starts and ends around the probed block.  Each
+and the same for sequences that share their first blocks, with sharing that starts
+and ends around the probed block.  Launches of enough shared units cut every sequence
+at the same positions: batches past one and two lanes' worth of sequences, beside
+sequences that share nothing, and on both sides of the rule.  Each
 output is compared with the float64 oracle over every element, and with the
 one-work-group-per-pair call, whose partial sums differ only in order.
 """
@@ -65,13 +67,45 @@ CASES = {
     "shared_short_of_the_probed_block": ([600, 700, 800], 8, 2, 128, None, [496]),
     "shared_group_16": ([30, 700, 9], 16, 1, 128, 40000, [2100]),
 }
+# the same, cut at the same positions
+ALIGNED = {
+    "agents": ([5 + (131 * i) % 900 for i in range(40)], 32, 8, 128, None, [3531, 3000, 4064]),
+    "past_two_waves_of_lengths": ([1 + (37 * i) % 300 for i in range(140)], 4, 4, 64, None, [2300, 2516]),
+    "two_heads": ([30 + (171 * i) % 700 for i in range(60)], 8, 2, 128, 40000, [7500]),
+    "beside_short_ones": ([1 + (131 * i) % 300 for i in range(40)], 16, 8, 128, None, [5600, 5616, 5500, 0]),
+}
+
+
+def plan_and_output(args, bound, scale):
+    """(aligned, units of a range or piece) of a call with its workspace, from the
+    workspace's end, and the call's output; args as the binding takes them."""
+    from paper_2608_14624_amd import ops
+    q, k_pool, _, bt, _ = args
+    batch, hq, d = q.shape
+    num_blocks, hkv = k_pool.shape[:2]
+    need = ops.paged_decode_workspace_bytes(batch, bound, hq, hkv, d)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")     # NaN everywhere
+    out = torch.full_like(q, float("nan"))
+    assert ops.cs_paged_decode_attn_ws_raw(*(t.data_ptr() for t in args), batch, bound, bt.shape[1], num_blocks,
+                                           hq, hkv, d, 16, scale, ws.data_ptr(), need, out.data_ptr()) == ops.CS_OK
+    torch.cuda.synchronize()
+    return ws[-8:].view(torch.int32).tolist(), out
 
 
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_ranges_match_oracle(name):
+    check_case(name, CASES[name], False)
+
+
+@pytest.mark.parametrize("name", sorted(ALIGNED))
+def test_aligned_pieces_match_oracle(name):
+    check_case(name, ALIGNED[name], True)
+
+
+def check_case(name, case, aligned):
     from paper_2608_14624_amd import ops
-    lens, hq, hkv, d, bound = CASES[name][:5]
-    wl = workload(lens, hq, hkv, d, *CASES[name][5:])
+    lens, hq, hkv, d, bound = case[:5]
+    wl = workload(lens, hq, hkv, d, *case[5:])
     q, seq_lens = decode_view(wl)
     assert poison_tails(wl) > 0 or all(n % 16 == 0 for n in seq_lens)
     bound = bound or int(seq_lens.max())
@@ -84,6 +118,9 @@ def test_ranges_match_oracle(name):
     args = (dev(q), dev(wl.k_pool), dev(wl.v_pool), dev(bt), dev(seq_lens))
     out = torch.full_like(args[0], float("nan"))
     ops.cs_paged_decode_attn(*args, out, max_seq_len=bound, scale=wl.scale)
+    plan, again = plan_and_output(args, bound, wl.scale)
+    assert plan[0] == aligned
+    assert torch.equal(out.view(torch.int16), again.view(torch.int16))
     plain = torch.full_like(out, float("nan"))
     p = [t.data_ptr() for t in args]
     assert ops.cs_paged_decode_attn_raw(*p, len(lens), bound, bt.shape[1], wl.num_blocks, hq, hkv, d,
@@ -126,6 +163,41 @@ def oracle_rows(wl, q, seq_lens):
                                           seq_lens.astype(np.int32) - 1,
                                           np.arange(wl.batch + 1, dtype=np.int32), hq, hkv, wl.scale,
                                           samples).reshape(wl.batch, hq, wl.head_dim)
+
+
+@pytest.mark.parametrize("d,length,sharing,aligned", [
+    (64, 2400, 63, True),      # one agent: a little over 36 units per range and sequence that shares
+    (64, 2300, 63, False),     # a little under
+    (64, 9000, 1, False),      # one pair among sequences of their own
+    (64, 9300, 16, True),      # a quarter of the batch
+    (64, 12000, 15, False),    # less, and more units
+    (128, 1800, 63, True),
+    (128, 1700, 63, False),
+    (128, 9000, 1, False),
+])
+def test_pieces_are_aligned_where_enough_is_shared(d, length, sharing, aligned):
+    """Aligned pieces are for batches that mostly share: one pair of sequences
+    with the same block at the probed index does not move a batch to them.  Block
+    ids elsewhere are any: what they hold only has to be the same in both calls."""
+    from paper_2608_14624_amd import ops
+    batch, hq, hkv = 64, 16, 8
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("lengths are for 256 compute units")
+    rng = np.random.default_rng(17)
+    bt = rng.integers(0, 256, size=(batch, -(-length // 16)), dtype=np.int32)
+    bt[:, 31] = np.maximum(np.arange(batch) - sharing, 0) + 20
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16)
+               for s in ((batch, hq, d), (256, hkv, 16, d), (256, hkv, 16, d)))
+    args = (q, k, v, dev(bt), dev(np.full(batch, length, np.int32)))
+    print(f"[case] aligned rule D={d} L={length} sharing={sharing}", flush=True)
+    (took, _), out = plan_and_output(args, length, d ** -0.5)
+    assert took == aligned
+    plain = torch.full_like(out, float("nan"))
+    assert ops.cs_paged_decode_attn_raw(*(t.data_ptr() for t in args), batch, length, bt.shape[1], 256, hq, hkv,
+                                        d, 16, d ** -0.5, plain.data_ptr()) == ops.CS_OK
+    torch.cuda.synchronize()
+    assert (out.double() - plain.double()).abs().max().item() <= MAX_ABS
 
 
 @pytest.mark.parametrize("anchors", [None, [1200]])
@@ -180,6 +252,26 @@ def test_ranges_take_a_negative_block_id_as_zeros(d):
     assert np.isfinite(got).all() and np.isfinite(plain).all()
     assert np.abs(plain - ref).max() <= MAX_ABS
     assert np.abs(got - ref).max() <= MAX_ABS
+
+
+def test_ranges_of_a_permuted_batch():
+    """A sequence is cut where the whole batch puts its cuts, so another order may
+    change low bits of its row, and no more than the roundings of the bf16
+    probabilities and output."""
+    lens = [300 + (811 * i) % 5000 for i in range(24)]
+    wl = workload(lens, 32, 8, 128)
+    q, seq_lens = decode_view(wl)
+    ref = oracle_rows(wl, q, seq_lens)
+    perm = np.random.default_rng(5).permutation(wl.batch)
+    kw = dict(bound=int(seq_lens.max()), scale=wl.scale)
+    outs = []
+    for order in (np.arange(wl.batch), perm):
+        args = (dev(q[order]), dev(wl.k_pool), dev(wl.v_pool), dev(wl.block_tables[order]), dev(seq_lens[order]))
+        (_, per), out = plan_and_output(args, **kw)
+        assert 1 < per < seq_lens.max() // 32
+        outs.append(oracle.bf16_bits_to_f64(bits(out)))
+        assert np.abs(outs[-1] - ref[order]).max() <= MAX_ABS
+    assert np.abs(outs[1] - outs[0][perm]).max() <= MAX_ABS
 
 
 @pytest.mark.parametrize("anchors", [None, [800]])
