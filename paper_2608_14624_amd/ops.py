@@ -485,7 +485,10 @@ def cs_paged_decode_attn(q, k_pool, v_pool, block_tables, seq_lens, out, *, max_
     workspace of ``cs_paged_decode_attn_ws`` is allocated here, from the
     caching allocator's pool of the launch's stream (the C call itself
     allocates nothing; on the per-thread stream, which has no pool of its own,
-    the call without a workspace is made)."""
+    the call without a workspace is made).  A row's low bits may depend on the
+    rest of the batch (``cs_paged_decode_attn_raw`` is independent of it).  Under
+    capture the workspace is the capture's own only with ``torch.cuda.graph``;
+    a stream captured by other means takes the raw calls."""
     dev = q.device
     _require_tensors(dev, q.get_device(), ("q", q, _BF16), ("k_pool", k_pool, _BF16),
                      ("v_pool", v_pool, _BF16), ("out", out, _BF16),

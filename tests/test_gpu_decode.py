@@ -339,22 +339,28 @@ def test_decode_private_recipe_scaled_down():
 
 
 def decode_bits(q, k_pool, v_pool, bt, seq_lens, scale):
+    """Output bits of the call with one work-group per sequence and KV head."""
     from paper_2608_14624_amd import ops
     qd = dev_bf16(q)
     out = torch.empty_like(qd)
-    ops.cs_paged_decode_attn(qd, k_pool, v_pool, torch.from_numpy(np.ascontiguousarray(bt)).cuda(),
-                             torch.from_numpy(np.ascontiguousarray(seq_lens)).cuda(), out,
-                             max_seq_len=int(seq_lens.max()), scale=scale)
+    btd = torch.from_numpy(np.ascontiguousarray(bt)).cuda()
+    lens = torch.from_numpy(np.ascontiguousarray(seq_lens)).cuda()
+    batch, hq, d = qd.shape
+    status = ops.cs_paged_decode_attn_raw(qd.data_ptr(), k_pool.data_ptr(), v_pool.data_ptr(), btd.data_ptr(),
+                                          lens.data_ptr(), batch, int(seq_lens.max()), btd.shape[1],
+                                          k_pool.shape[0], hq, k_pool.shape[1], d, 16, scale, out.data_ptr())
+    assert status == ops.CS_OK
     torch.cuda.synchronize()
     return out.view(torch.int16).cpu().numpy()
 
 
-def test_decode_is_independent_of_batch_order():
+@pytest.mark.parametrize("longest", [152, 1500])
+def test_decode_is_independent_of_batch_order(longest):
     """The kernel runs the sequences longest first (every work-group ranks
     the lengths itself, ties by index): reordering the batch, with many
     equal lengths, permutes the output rows and changes no bit of them."""
     invs = [Invocation(i % 5, 1 + (i % 4) * 17) for i in range(40)]   # ten of each length class
-    wl = build_workload("order", 3, [30, 61, 16, 100, 5], invs, num_q_heads=8, num_kv_heads=2,
+    wl = build_workload("order", 3, [30, 61, 16, longest - 52, 5], invs, num_q_heads=8, num_kv_heads=2,
                         head_dim=128, num_blocks=1024)
     q, seq_lens = decode_view(wl)
     assert len(np.unique(seq_lens)) < len(seq_lens)
