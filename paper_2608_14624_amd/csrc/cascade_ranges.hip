@@ -471,7 +471,7 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
 
 // One work-group per (sequence, KV head): combines the pieces of its group's
 // shared prefix and of its own keys.  A thread holds four features of one row;
-// as many teams of threads as fit share the pieces, each taking kMergeStep
+// as many teams of threads as fit and have work share the pieces, each taking kMergeStep
 // at a time with their loads in flight together, and meet in LDS.  (Steps of 8
 // with the last piece read again past the end: 9.4 us where this takes 6.5.)
 constexpr int kMergeStep = 4;
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(kMergeThreads) void cascade_ranges_merge_kernel(Cas
   const int shared_row = (group_cb + cb + w_cb) * p.width + rho % p.width;
   const int own_row = own_at + (r + w_own - own_w) * p.group + hj;
   const int n = n_shared + n_own;
-  const int teams = min(kMergeThreads / elems, max(1, ceil_div(n, kMergeStep)));   // as many as have work
+  const int teams = min(kMergeThreads / elems, max(1, ceil_div(n, kMergeStep)));
   float mx = -INFINITY, den = 0.f;
   f32x4 acc = f32x4{};
   if (team < teams) {
