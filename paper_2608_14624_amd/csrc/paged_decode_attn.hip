@@ -830,7 +830,10 @@ __global__ __launch_bounds__(kMergeThreads) void decode_ranges_merge_kernel(DecP
     first = r + w0;
     n = (before + units - 1) / per - w0 + 1;
   }
-  if (n <= 1) return;
+  // a sequence of one piece has its output; one without keys gets NaN here, as
+  // from one work-group per pair
+  if (units == 0) n = 0;
+  if (n == 1) return;
   const float c = p.scale_log2;
   const int elems = p.group * (D / 4);   // threads of a team
   const int teams = min(kMergeThreads / elems, max(1, ceil_div(n, kMergeStep)));

@@ -254,6 +254,32 @@ def test_ranges_take_a_negative_block_id_as_zeros(d):
     assert np.abs(got - ref).max() <= MAX_ABS
 
 
+@pytest.mark.parametrize("lens", [[0], [700, 0, 1, 2500, 0], [0, 0, 90, 4000]])
+def test_ranges_write_every_row(lens):
+    """A row without keys holds no number, and no other row feels it; nothing of
+    what the output held before is left, as in the call without a workspace."""
+    wl = workload([max(n, 1) for n in lens], 8, 2, 128)
+    q, seq_lens = decode_view(wl)
+    lens = np.asarray(lens, np.int32)
+    args = (dev(q), dev(wl.k_pool), dev(wl.v_pool), dev(wl.block_tables), dev(lens))
+    bound = max(int(seq_lens.max()), 200)
+    if bound > wl.block_tables.shape[1] * 16:
+        bt = np.zeros((len(lens), -(-bound // 16)), np.int32)
+        bt[:, :wl.block_tables.shape[1]] = wl.block_tables
+        args = args[:3] + (dev(bt),) + args[4:]
+    from paper_2608_14624_amd import ops
+    out = torch.full_like(args[0], 3.0)
+    ops.cs_paged_decode_attn(*args, out, max_seq_len=bound, scale=wl.scale)
+    torch.cuda.synchronize()
+    got = oracle.bf16_bits_to_f64(bits(out))
+    ref = oracle_rows(wl, q, seq_lens)
+    for r, n in enumerate(lens):
+        if n == 0:
+            assert np.isnan(got[r]).all()
+        else:
+            assert np.abs(got[r] - ref[r]).max() <= MAX_ABS
+
+
 def test_ranges_of_a_permuted_batch():
     """A sequence is cut where the whole batch puts its cuts, so another order may
     change low bits of its row, and no more than the roundings of the bf16
