@@ -133,22 +133,22 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
     int units, blocks;
     group_lists(b + lane, units, blocks);
     const int incl = wave_scan(blocks * units), incl_b = wave_scan(blocks);
-    if (writes_plan && b + lane < p.num_groups) {
-      for (int s = group_at[b + lane]; s < group_at[b + lane + 1]; ++s) {
-        int32_t* rec = p.plan + kPlanHead + kPlanSeq * s;
-        rec[0] = s - group_at[b + lane];
-        rec[1] = units;
-        rec[2] = shared_end + incl - blocks * units;
-        rec[3] = col_blocks + incl_b - blocks;
-      }
+    // a group's part of the plan, at its first sequence; the others take it from there
+    if (writes_plan && b + lane < p.num_groups && group_at[b + lane + 1] > group_at[b + lane]) {
+      int32_t* rec = p.plan + kPlanHead + kPlanSeq * group_at[b + lane];
+      rec[1] = units;
+      rec[2] = shared_end + incl - blocks * units;
+      rec[3] = col_blocks + incl_b - blocks;
     }
     shared_end += __builtin_amdgcn_readlane(incl, 63);
     col_blocks += __builtin_amdgcn_readlane(incl_b, 63);
   }
+  if (writes_plan) __syncthreads();
   int total = shared_end;
   for (int b = 0; b < p.batch; b += 64) {
     const int s = b + lane;
     const int len = len_next;
+    int first = 0;                         // of the sequence's group
     len_next = s + 64 < p.batch ? p.seq_lens[s + 64] : 0;
     int own = 0;
     if (s < p.batch) {
@@ -157,14 +157,21 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
         const int mid = (lo + hi + 1) >> 1;
         if (group_at[mid] <= s) lo = mid; else hi = mid - 1;
       }
+      first = group_at[lo];
       own = max(len - max(group_len[lo], 0), 0);
       own_len[s] = own;
     }
     const int units = units_of(own);
     const int incl = wave_scan(units);
     if (writes_plan && s < p.batch) {
-      p.plan[kPlanHead + kPlanSeq * s + 4] = total + incl - units;
-      p.plan[kPlanHead + kPlanSeq * s + 5] = units;
+      int32_t* rec = p.plan + kPlanHead + kPlanSeq * s;
+      const int32_t* of_group = p.plan + kPlanHead + kPlanSeq * first;
+      rec[0] = s - first;
+      rec[1] = of_group[1];
+      rec[2] = of_group[2];
+      rec[3] = of_group[3];
+      rec[4] = total + incl - units;
+      rec[5] = units;
     }
     total += __builtin_amdgcn_readlane(incl, 63);
   }
