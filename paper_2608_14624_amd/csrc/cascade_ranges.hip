@@ -570,16 +570,30 @@ __global__ __launch_bounds__(kMergeThreads) void cascade_ranges_merge_kernel(Cas
 constexpr int kCascadeGroupsPerCu128 = 4;
 constexpr int kCascadeGroupsPerCu64 = 8;
 
-// Ranges need room: besides a piece per range, every list may be cut once
-// more, and the plan itself takes some rows; what is left bounds the number of
-// pieces, so a small batch's workspace may allow only ranges longer than an equal
-// share.  The host knows the bounds of the lengths alone: with prefixes at
-// their bound and own parts at 0.4 of theirs, ranges are taken while they come
-// out at most three times as long as an equal share.  us a call in chunks ->
-// in ranges, with that ratio: 128 sequences of 8 agents 172 -> 138 (0.5), 48 of
-// them at head_dim 64 68 -> 55 (2.4), 16 of 4 agents 70 -> 45 (2.6), 64 of 4 with
-// at most 1000 own keys 75 -> 85 (3.4), 24 of one agent on 16000 keys 54 -> 113
-// (5.1).
+// Ranges need room: besides a piece per range, every list may be cut once more,
+// and the plan itself takes some rows; what is left bounds the number of pieces,
+// so a small batch's workspace may allow only ranges `stretch` times as long as an
+// equal share.  And a prefix is streamed once for every column block of its
+// group, by other waves at other times, in units of up to four tiles.
+// The host knows the bounds of the lengths alone, so it compares two estimates,
+// with prefixes at their bound and own parts at 0.4 of theirs.  In us, for
+// shared, own and distinct shared (once per group) units per range, fitted to 296
+// calls (32 / 8, 64 / 8, 16 / 16 and 8 / 2 heads at 64 and 128, 8 to 160 sequences
+// of 1 to 12 agents, prefixes of 1000 to 10000 keys, own bounds of 200 to 4000):
+// chunks 21 + 1.1 shared + 3 own + 2.5 distinct, ranges (0.8 + 1.2 x tiles / 4 x
+// share of shared units) x units per range + 1.5 (own + distinct).  Ranges are
+// taken where they come out 5% ahead: on average 1% slower than the better of the
+// two, where a rule on the stretch alone (3) was 6%.  us a call, chunks -> ranges:
+//   128 sequences of 8 agents, 32 / 8 heads of 128       190 -> 154   taken
+//   16 of 4 agents, prefixes of 10000, own 4000           85 -> 59    taken
+//   128 of one agent, 64 / 8, 8000, own 2500             185 -> 169   taken
+//   64 of one agent, 32 / 8, 8000, own 600                56 -> 90
+//   128 of one agent, 64 / 8, 2300, own 600               67 -> 115
+//   160 of 4 agents, 32 / 8 of 64, 8000, own 600          59 -> 84
+//   96 of 3 agents, 64 / 8, 10000, own 1200               97 -> 106   taken
+//   128 of 8 agents, 32 / 8, 10000, own 200              105 -> 88
+// With one query head per KV head, whose partials are small, long ranges end
+// late: at a stretch of 2.4, 32 sequences of 8 agents, 16 / 16 heads, 183 -> 266.
 CascadeRanges cascade_ranges(int batch, int num_groups, int max_group_seqs, int max_shared_len,
                              int max_rest_len, int num_q_heads, int num_kv_heads, int head_dim,
                              long long parts, int cus) {
@@ -595,9 +609,17 @@ CascadeRanges cascade_ranges(int batch, int num_groups, int max_group_seqs, int 
   const long long room = rows - fixed;
   if (room <= 0 || rows > 0x7fffffffLL) return geo;
   const int ranges = std::max(1, (head_dim == 128 ? kCascadeGroupsPerCu128 : kCascadeGroupsPerCu64) * cus / num_kv_heads);
-  const double shared = (double)(((long long)batch * group + width - 1) / width) * max_shared_len / kUnitKeys;
-  const double own = 0.4 * batch * max_rest_len / kUnitKeys;
-  if ((shared * width + own * group) / room > 3. * (shared + own) / ranges) return geo;
+  const double per_unit = 1. / ((double)kUnitKeys * ranges);
+  const double shared = per_unit * (((long long)batch * group + width - 1) / width) * max_shared_len;
+  const double distinct = std::min(shared, per_unit * num_groups * max_shared_len);
+  const double own = per_unit * 0.4 * batch * max_rest_len;
+  const double share = shared + own;
+  const double stretch = share > 0. ? (shared * width + own * group) * ranges / (share * room) : 1.;
+  if (stretch > (group == 1 ? 2. : 3.)) return geo;
+  const double chunks_us = 21. + 1.1 * shared + 3. * own + 2.5 * distinct;
+  const double ranges_us = std::max(stretch, 1.) * (0.8 * share + 1.2 * width / (kMaxTiles * kTileRows) * shared) +
+                           1.5 * (own + distinct);
+  if (ranges_us > 0.95 * chunks_us) return geo;
   geo.ranges = ranges;
   geo.width = width;
   geo.rows = (int)rows;

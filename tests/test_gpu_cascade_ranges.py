@@ -31,16 +31,65 @@ def dev(a):
 
 
 def takes_ranges(batch, groups, max_seqs, hq, hkv, d, max_shared, max_rest, cus=256):
-    """The rule of the launch: ranges at most three times as long as an equal share,
-    for prefixes at their bound and own parts at 0.4 of theirs."""
+    """The rule of the launch: two estimates from the host's bounds."""
     g = hq // hkv
     parts = -(-max_shared // 1024) + -(-max_rest // 1024)
     width = min(64, -(-max_seqs * g // 16) * 16)
     room = (parts * batch * hq - (6 * batch + 9) // 2) // hkv - (
         (batch * g // width + groups + 2) * width + (batch + 2) * g)
     ranges = max(1, (4 if d == 128 else 8) * cus // hkv)
-    shared, own = -(-batch * g // width) * max_shared / 32, 0.4 * batch * max_rest / 32
-    return room > 0 and (shared * width + own * g) / room <= 3 * (shared + own) / ranges
+    shared = -(-batch * g // width) * max_shared / 32 / ranges
+    distinct = min(shared, groups * max_shared / 32 / ranges)
+    own = 0.4 * batch * max_rest / 32 / ranges
+    if room <= 0:
+        return False
+    stretch = (shared * width + own * g) * ranges / ((shared + own) * room)
+    return stretch <= (2 if g == 1 else 3) and (
+        max(stretch, 1) * (0.8 * (shared + own) + 1.2 * width / 64 * shared) + 1.5 * (own + distinct)
+        <= 0.95 * (21 + 1.1 * shared + 3 * own + 2.5 * distinct))
+
+
+@pytest.mark.parametrize("expect,batch,groups,max_seqs,hq,hkv,d,max_shared,max_rest", [
+    (True, 128, 8, 16, 32, 8, 128, 8000, 4096),
+    (True, 16, 4, 4, 32, 8, 128, 10000, 4000),
+    (True, 160, 4, 40, 32, 8, 64, 4000, 4000),
+    # prefixes streamed once per column block, and little besides
+    (False, 128, 1, 128, 32, 8, 128, 8000, 200),
+    (False, 64, 1, 64, 32, 8, 128, 8000, 600),
+    (False, 128, 1, 128, 64, 8, 128, 2300, 600),
+    (False, 160, 4, 40, 32, 8, 64, 8000, 600),
+    (False, 600, 1, 600, 4, 1, 128, 3500, 1500),
+    # long ranges for want of room
+    (False, 32, 8, 4, 16, 16, 128, 10000, 2500),
+])
+def test_launches_where_ranges_are_slower_run_in_chunks(expect, batch, groups, max_seqs, hq, hkv, d, max_shared,
+                                                        max_rest):
+    """A launch in ranges leaves its plan behind its partials, first the few units of
+    a range; in chunks the place holds the mark set here, or the bits of a float."""
+    from paper_2608_14624_amd import ops
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule is evaluated for 256 compute units")
+    assert takes_ranges(batch, groups, max_seqs, hq, hkv, d, max_shared, max_rest) == expect
+    bound = max_shared + max_rest
+    bt = torch.zeros(batch, -(-bound // 16), dtype=torch.int32, device="cuda")
+    pool = torch.ones(4, hkv, 16, d, dtype=torch.bfloat16, device="cuda")
+    q = torch.ones(batch, hq, d, dtype=torch.bfloat16, device="cuda")
+    out = torch.empty_like(q)
+    sizes = [batch // groups] * groups
+    cu = dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+    need = ops.cs_cascade_decode_workspace_bytes(batch, hq, d, max_shared, max_rest)
+    ws = torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda")
+    print(f"[case] cascade route B={batch} groups={groups} Hq={hq} Hkv={hkv} D={d} {max_shared}+{max_rest}", flush=True)
+    ops.cs_cascade_decode_attn(q, pool, pool, bt, dev(np.full(batch, 48, np.int32)), cu,
+                               dev(np.full(groups, 32, np.int32)), out, max_seq_len=bound, max_group_seqs=max_seqs,
+                               max_shared_len=max_shared, max_rest_len=max_rest, scale=d ** -0.5, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out, torch.ones_like(out))
+    parts = -(-max_shared // 1024) + -(-max_rest // 1024)
+    rows = (parts * batch * hq - (6 * batch + 9) // 2) // hkv
+    at = 4 * (parts * batch * hq * d + 2 * rows * hkv)                     # the plan
+    per = ws[at:at + 4].view(torch.int32).item()
+    assert (0 < per < 1000) == expect
 
 
 def build(groups, hq, hkv, d):
