@@ -37,6 +37,7 @@
 #include "decode_common.h"
 #include "internal.h"
 
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
@@ -92,7 +93,7 @@ struct CascadeCursor {
 };
 
 template <int D>
-__global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
+__global__ __launch_bounds__(64, D == 64 ? 2 : 1) void cascade_ranges_kernel(CascadeParams p) {
   constexpr int vStride = D + 16;      // padded by 32 B: transposing reads without bank conflicts
   constexpr int DC = D / 32;
   constexpr int DT = D / 16;
@@ -301,6 +302,9 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
   const uint16_t* kbase = p.k_pool + (size_t)g * tile_elems;
   const uint16_t* vbase = p.v_pool + (size_t)g * tile_elems;
   const float c = p.scale_log2;
+  const float drop = 8.f / c;
+  // a unit whose logits are all -inf weighs 0 relative to this, not NaN
+  const float lowest = -FLT_MAX / fmaxf(c, 1.f);
 
   bf16x8 kreg[2][DC];
   bf16x8 vreg[kVLoads];
@@ -338,6 +342,7 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
   // took 10 us); rows past the list's last hold q = 0.
   auto run_piece = [&](auto nt_tag) __attribute__((always_inline)) {
     constexpr int NT = decltype(nt_tag)::value;
+    constexpr int kEvery = NT == 1 ? 1 : 8;
     // Q^T operands: column j of tile t is row rho + 16 t + j of the list
     bf16x8 qreg[NT][DC];
 #pragma unroll
@@ -352,12 +357,12 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
       }
     }
     f32x4 oacc[NT][DT];
-    float m_run[NT], l_run[NT];
+    float m_run[NT], m_max[NT], l_run[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) oacc[t][dt] = f32x4{};
-      m_run[t] = -INFINITY;
+      m_run[t] = m_max[t] = -INFINITY;
       l_run[t] = 0.f;
     }
     for (;;) {
@@ -404,20 +409,28 @@ __global__ __launch_bounds__(64) void cascade_ranges_kernel(CascadeParams p) {
             for (int rr = 0; rr < 4; ++rr)
               s[t][mt][rr] = key0 + 16 * mt + 4 * qd + rr < cur.len ? s[t][mt][rr] : -INFINITY;
       }
+      // The reference maximum of the probabilities moves where a row's max grew by
+      // more than 2^8, and every kEvery units to the unit's own (but never 2^8
+      // below the largest so far): the largest probabilities of those units are
+      // then exact in bf16.  Relative error against float64, with a reference that
+      // only grew, now, and in chunks and segments: 128 sequences of 8 agents
+      // 0.00234, 0.00228, 0.00231 in the same time (154 us); 48 with 1000 shared
+      // and up to 4000 own keys 0.00232, 0.00221, 0.00226.  Every unit for own
+      // keys is free; for stacked rows every fourth costs 1-2%, every unit 2-8%.
       float mloc[NT];
       bool grow = false;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        mloc[t] = quad_max(fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3])),
-                                 fmaxf(fmaxf(s[t][1][0], s[t][1][1]), fmaxf(s[t][1][2], s[t][1][3]))));
+        mloc[t] = fmaxf(quad_max(fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3])),
+                                       fmaxf(fmaxf(s[t][1][0], s[t][1][1]), fmaxf(s[t][1][2], s[t][1][3])))),
+                        lowest);
+        m_max[t] = fmaxf(m_max[t], mloc[t]);
         grow |= (mloc[t] - m_run[t]) * c > 8.f;      // true for every row at a piece's first unit
       }
-      // lazy rescale: the reference max moves only when a row's max grew by more
-      // than 2^8 in probability
-      if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+      if (cur.x % kEvery == 0 || __builtin_amdgcn_ballot_w64(grow) != 0) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const float m_new = fmaxf(m_run[t], mloc[t]);
+          const float m_new = fmaxf(mloc[t], m_max[t] - drop);
           const float alpha = __builtin_amdgcn_exp2f((m_run[t] - m_new) * c);
           m_run[t] = m_new;
           l_run[t] *= alpha;

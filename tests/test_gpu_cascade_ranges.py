@@ -210,3 +210,42 @@ def test_cascade_ranges_take_a_negative_block_id_as_zeros():
                                          samples).reshape(wl.batch, hq, d)
     got = oracle.bf16_bits_to_f64(out.view(torch.int16).cpu().numpy().view(np.uint16))
     assert np.abs(got - ref).max() <= MAX_ABS
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_cascade_ranges_are_as_close_as_the_chunks(d):
+    """Long ranges lose no precision against segments of 1024 keys, which the same
+    batch takes with tight bounds.  The 2-norm of about 100,000 independent roundings
+    repeats to about 0.2%, so 1% is five times that."""
+    from paper_2608_14624_amd import ops
+    batch, hq, hkv, shared_len = 48, 32, 8, 1008
+    rng = np.random.default_rng(23)
+    own = rng.integers(2000, 2500, size=batch)
+    seq_lens = (own + shared_len).astype(np.int32)
+    bound = 20 * 1024
+    bt = rng.integers(0, 600, size=(batch, bound // 16), dtype=np.int32)   # any blocks
+    for r in range(batch):
+        bt[r, :shared_len // 16] = bt[r - r % 16, :shared_len // 16]
+    pools = [rng.standard_normal((600, hkv, 16, d), dtype=np.float32) for _ in range(2)]
+    q = torch.from_numpy(rng.standard_normal((batch, hq, d), dtype=np.float32)).to("cuda", torch.bfloat16)
+    k, v = (torch.from_numpy(x).to("cuda", torch.bfloat16) for x in pools)
+    args = (q, k, v, dev(bt), dev(seq_lens), dev(np.arange(0, 49, 16, dtype=np.int32)),
+            dev(np.full(3, shared_len, np.int32)))
+    kd, vd = k.double(), v.double()
+    ref = torch.empty(batch, hq, d, dtype=torch.float64, device="cuda")
+    for r in range(batch):
+        n = int(seq_lens[r])
+        ids = args[3][r, :-(-n // 16)].long()
+        kr, vr = (x[ids].transpose(0, 1).reshape(hkv, -1, d)[:, :n] for x in (kd, vd))
+        p = torch.softmax((q[r].double().view(hkv, -1, d) @ kr.transpose(1, 2).contiguous()) * d ** -0.5, dim=-1)
+        ref[r] = (p @ vr.contiguous()).reshape(hq, d)
+    errs = []
+    for rest in (2500, bound - shared_len):
+        assert takes_ranges(batch, 3, 16, hq, hkv, d, shared_len, rest) == (rest > 2500)
+        out = torch.full_like(q, float("nan"))
+        ops.cs_cascade_decode_attn(*args, out, max_seq_len=bound, max_group_seqs=16, max_shared_len=shared_len,
+                                   max_rest_len=rest, scale=d ** -0.5)
+        torch.cuda.synchronize()
+        errs.append(((out.double() - ref).norm() / ref.norm()).item())
+    print(f"[case] cascade precision D={d}: chunks {errs[0]:.6f}, ranges {errs[1]:.6f}", flush=True)
+    assert errs[1] <= 1.01 * errs[0]

@@ -215,11 +215,13 @@ def test_ranges_are_as_close_as_the_call_without_a_workspace(d, anchors):
     assert err <= 1.01 * err_plain
 
 
+@pytest.mark.parametrize("scale", [None, 1.5])
 @pytest.mark.parametrize("d", [64, 128])
-def test_ranges_with_logits_of_minus_infinity(d):
+def test_ranges_with_logits_of_minus_infinity(d, scale):
     """32 keys whose logits are -inf, at the first unit of a range, inside one
-    and at a sequence's start, weigh nothing."""
+    and at a sequence's start, weigh nothing, also where scale log2(e) is above 1."""
     wl = workload([3000, 700], 4, 4, d)
+    wl.scale = scale or wl.scale
     q, seq_lens = decode_view(wl)
     q[:, :, 0] = 0x3F80                                    # 1.0
     ref_pool = wl.k_pool.copy()
