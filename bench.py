@@ -354,6 +354,7 @@ def bench_copy(args, dev):
     k_pool = torch.from_numpy(wl.k_pool.view(np.int16)).view(torch.bfloat16).to(dev)
     v_pool = torch.from_numpy(wl.v_pool.view(np.int16)).view(torch.bfloat16).to(dev)
     hkv, d = wl.num_kv_heads, wl.head_dim
+    decode_kernel = cascade_kernel = None
     if args.component in ("decode", "cascade_decode"):
         from paper_2608_14624_amd.workload import cascade_view, decode_view
         # the batch ordered by agent group (the order cascade decode needs;
@@ -377,6 +378,9 @@ def bench_copy(args, dev):
             [bt_np[r, :-(-int(L) // 16)] for r, L in enumerate(seq_lens_np)])))
         unique_bytes = unique_blocks * hkv * 16 * d * 2 * 2 + qo
         moved = unique_bytes
+        decode_kernel = (f"decode_ranges_kernel<{d}> + decode_ranges_merge_kernel<{d}>"
+                         if ops.paged_decode_workspace_bytes(wl.batch, max_len, wl.num_q_heads, hkv, d) > 0
+                         else f"paged_decode_attn_kernel<{d}, false>")
         if args.component == "decode":
             def fn():
                 ops.cs_paged_decode_attn(q, k_pool, v_pool, bt, seq_lens, out,
@@ -388,6 +392,12 @@ def bench_copy(args, dev):
                                                          cv["max_shared_len"],
                                                          cv["max_rest_len"])
             ws = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+            # the library's rule for the route is not exported; the serving
+            # configuration's launches are the traced ones in profiles/
+            cascade_kernel = f"cascade_ranges_kernel<{d}> + cascade_ranges_merge_kernel<{d}>"
+            if args.workload != "decode_batch":
+                cascade_kernel += (f", or shared_prefix_partials_kernel<{d}> + paged_decode_attn_kernel<{d}, true>"
+                                   f" + cascade_merge_kernel<{d}> (the launch rule's choice)")
 
             def fn():
                 ops.cs_cascade_decode_attn(q, k_pool, v_pool, bt, seq_lens, cu, shared, out,
@@ -463,13 +473,11 @@ def bench_copy(args, dev):
             ops.cs_kv_offload(ids, k_pool, v_pool, host_k, host_v, stream=stream)
         peak, bound, unit_desc = PEAK_PCIE5_X16_GBS, "host_link", f"{n} blocks"
     kernel, sources = {
-        "decode": ("decode_ranges_kernel<128> + decode_ranges_merge_kernel<128>",
-                   ("paper_2608_14624_amd/csrc/paged_decode_attn.hip",
-                    "paper_2608_14624_amd/csrc/decode_common.h")),
-        "cascade_decode": ("cascade_ranges_kernel<128> + cascade_ranges_merge_kernel<128>",
-                           ("paper_2608_14624_amd/csrc/cascade_ranges.hip",
-                            "paper_2608_14624_amd/csrc/decode_common.h",
-                            "paper_2608_14624_amd/csrc/internal.h")),
+        "decode": (decode_kernel, ("paper_2608_14624_amd/csrc/paged_decode_attn.hip",
+                                   "paper_2608_14624_amd/csrc/decode_common.h")),
+        "cascade_decode": (cascade_kernel, ("paper_2608_14624_amd/csrc/cascade_ranges.hip",
+                                            "paper_2608_14624_amd/csrc/decode_common.h",
+                                            "paper_2608_14624_amd/csrc/internal.h")),
         "kv_write": ("kv_write_kernel", ("paper_2608_14624_amd/csrc/kv_copy.hip",)),
         "kv_offload": ("kv_offload_kernel", ("paper_2608_14624_amd/csrc/kv_copy.hip",
                                              "paper_2608_14624_amd/csrc/block_copy.h")),

@@ -336,11 +336,10 @@ int64_t cs_paged_decode_workspace_bytes(int32_t batch, int32_t max_seq_len, int3
  * shared_lens[g] .. seq_lens[r]-1 are attended in segments of 1024 keys,
  * each leaving a partial too, and a last launch merges all partials of a
  * row with log-sum-exp weights.  Where the workspace has the room (batches up
- * to 1024, and lengths and groups such that the partials leave ranges of a
- * reasonable size), both are instead counted in units of 32 keys and dealt in
- * equal ranges to a few one-wave work-groups per compute unit, whose partials
- * use the same workspace.  The output equals cs_paged_decode_attn's up to
- * rounding order.
+ * to 1024) and the bounds of the lengths let it be faster, both are instead
+ * counted in units of 32 keys and dealt in equal ranges to a few one-wave
+ * work-groups per compute unit, whose partials use the same workspace.  The
+ * output equals cs_paged_decode_attn's up to rounding order.
  *
  * Arguments (those of cs_paged_decode_attn, plus)
  *   cu_groups       device, int32 [num_groups + 1]: 0 = cu_groups[0] <= ...

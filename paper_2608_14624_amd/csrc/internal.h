@@ -188,9 +188,9 @@ hipError_t launch_shared_prefix_partials(const CascadeLaunch& a, hipStream_t str
 hipError_t launch_cascade_decode_rest(const CascadeLaunch& a, hipStream_t stream);
 
 // Cascade decode in ranges (cascade_ranges.hip), where the workspace of `parts`
-// chunks and segments has the room: both halves in one launch of `ranges`
-// one-wave work-groups per KV head, with `rows` partial rows per KV head
-// (ranges 0: the launches in chunks and segments).
+// chunks and segments has the room and they are estimated to be faster: both
+// halves in one launch of `ranges` one-wave work-groups per KV head, with `rows`
+// partial rows per KV head (ranges 0: the launches in chunks and segments).
 struct CascadeRanges {
   int ranges;
   int width;

@@ -958,13 +958,15 @@ __global__ __launch_bounds__(kThreads) void cascade_merge_kernel(DecParams p) {
 }  // namespace
 
 // Ranges or one work-group per (sequence, KV head): ranges win from a few
-// hundred keys on, at every batch.  32 / 8 heads of 128, us a call, one
-// work-group per pair -> ranges (with their merge): 1 sequence of 500-900 keys
-// 16.3 -> 8.0, 3 of 2000-6000 57 -> 19, 24 of 500-9000 123 -> 85, 64 of
-// 6000-9000 334 -> 308, 128 of 100-500 72 -> 36, 512 of 1000-2000 769 -> 507.
-// Below, and at head_dim 64 up to 512 keys while the pairs fit one round, the
-// merge launch is not paid for (8 sequences of 100-500 keys at 64: 8.5 -> 8.6,
-// 16 of them 8.9 -> 10.3 before the loads went through descriptors).
+// hundred keys on, at every batch.  us a call back to back, one work-group per pair
+// -> ranges with their merge: 32 / 8 heads of 128, 2 sequences of 84-140 keys 11.1 ->
+// 8.2, 3 of 2000-6000 49 -> 14, 24 of 500-9000 115 -> 67, 128 of 100-500 67 -> 35, 128 of
+// 4200-10800 676 -> 616; 32 / 8 heads of 64, 128 of 2000-6000 210 -> 181.
+// At head_dim 64 up to 512 keys, while the pairs fit one round, the merge launch is
+// not paid for (8 sequences of 100-500 keys 8.5 -> 8.6).  Past 512 a full round of
+// pairs of nearly equal lengths still loses up to 1.3 us to it, ragged ones gain (32
+// sequences, 32 / 8 heads: 448-560 keys 10.6 -> 11.4, 112-560 9.9 -> 9.6, 1600-2000
+// 23.9 -> 24.8, 400-2000 20.4 -> 19.5).
 DecodeGeometry decode_geometry(int batch, int max_seq_len, int num_kv_heads, int head_dim, int cus) {
   DecodeGeometry geo = {};
   if (batch < 1 || batch > kRangeMaxBatch || max_seq_len <= 128) return geo;

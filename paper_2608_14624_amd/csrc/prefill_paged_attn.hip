@@ -272,9 +272,17 @@ __device__ __forceinline__ bool even_tile(const Params& p, int wg, TileAt& t) {
 // heads of 128, 258 -> 225, and a quarter of them misses, 32 / 8 heads, 1569 ->
 // 1548; 64 of 20-1500 2928 -> 2872.
 // At head_dim 64 the code of the halves costs the ping-pong loop registers (33
-// spilled against 21): from kRoundsWithoutHalves rounds of the bound on, a ragged
-// launch goes without them (32 invocations of 586-3740 tokens: 1097 us with them,
-// and on another box 991 without, 1000 numbered over the longest).
+// spilled against 15 without): from kRoundsWithoutHalves rounds of the bound on, a
+// ragged launch goes without them.  us a call, with and without, 32 / 8 heads,
+// suffixes on 1500-2500 cached: 7 invocations of 200-900 tokens 113 and 125, 16 of
+// 100-400 94 and 110, 16 of 500-1800 547 and 533, 32 of 500-1800 1009 and 978, 32 of
+// 600-3700 2266 and 2204 (numbered over the longest 133, 114, 566, 989, 2211).
+//
+// In the lengths' own order the last round is what the lengths leave, and a few long
+// misses can leave it worse than the bound's numbering did by chance: 5 misses of
+// 4500-8100 tokens, 4 / 1 heads, 275 us against 246, 5 invocations of which 2 are
+// misses of 2500, 32 / 8, 152 against 141; of 420 calls drawn over the sizes of
+// serving 14 were more than 2% slower, most of them by 2-3%, and over 228 faster.
 enum class PPMode { kEven, kHalves, kRagged };
 constexpr int kRoundsWithoutHalves = 8;
 // Past this many invocations every work-group would read too many lengths (300
