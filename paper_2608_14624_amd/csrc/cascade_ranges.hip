@@ -94,11 +94,10 @@ struct CascadeCursor {
 
 template <int D>
 __global__ __launch_bounds__(64, D == 64 ? 2 : 1) void cascade_ranges_kernel(CascadeParams p) {
-  constexpr int vStride = D + 16;      // padded by 32 B: transposing reads without bank conflicts
+  constexpr int vStride = v_tile_stride(D);
   constexpr int DC = D / 32;
   constexpr int DT = D / 16;
-  constexpr int kRowChunks = D / 8;
-  constexpr int kVLoads = kChunk * kRowChunks / 64;
+  constexpr int kVLoads = kChunk * D / 8 / 64;
   __shared__ uint16_t vt[kChunk * vStride];
   // lengths of the sequences' own keys; first sequence and shared keys of the groups
   __shared__ int own_len[kRangeMaxBatch];
@@ -319,14 +318,6 @@ __global__ __launch_bounds__(64, D == 64 ? 2 : 1) void cascade_ranges_kernel(Cas
     id0 = bt[b0];
     id1 = bt[min(b0 + 1, (cu.len - 1) / kBlock)];
   };
-  const int tr_off = (4 * qd + (j >> 2)) * vStride + 4 * (j & 3);
-  auto v_frag = [&](int dt) -> bf16x8 {
-    const uint16_t* base = vt + tr_off + 16 * dt;
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base + 16 * vStride));
-    const i16x4 lohi[2] = {lo, hi};
-    return __builtin_bit_cast(bf16x8, lohi);
-  };
   // three cursors: the unit being computed, the one whose loads are in flight
   // behind it, and the one whose block ids are being read
   CascadeCursor cur = ids;
@@ -367,22 +358,7 @@ __global__ __launch_bounds__(64, D == 64 ? 2 : 1) void cascade_ranges_kernel(Cas
     }
     for (;;) {
       const int key0 = cur.x * kUnitKeys;
-#pragma unroll
-      for (int v = 0; v < kVLoads; ++v) {
-        const int cc = lane + 64 * v;
-        *reinterpret_cast<bf16x8*>(&vt[(cc / kRowChunks) * vStride + (cc % kRowChunks) * 8]) = vreg[v];
-      }
-      // rows past the end of the list (inside its last block, or the other half
-      // of a shared prefix's last unit) hold zeros: their probabilities are 0,
-      // but 0 times a stale NaN or Inf is NaN
-      if (key0 + kChunk > cur.len) {
-#pragma unroll
-        for (int v = 0; v < kVLoads; ++v) {
-          const int cc = lane + 64 * v;
-          if (key0 + cc / kRowChunks >= cur.len)
-            *reinterpret_cast<bf16x8*>(&vt[(cc / kRowChunks) * vStride + (cc % kRowChunks) * 8]) = bf16x8{};
-        }
-      }
+      store_v_tile<D>(vreg, lane, key0, cur.len, vt);
       f32x4 s[NT][2];
 #pragma unroll
       for (int t = 0; t < NT; ++t) s[t][0] = s[t][1] = f32x4{};
@@ -456,7 +432,7 @@ __global__ __launch_bounds__(64, D == 64 ? 2 : 1) void cascade_ranges_kernel(Cas
       }
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
-        const bf16x8 v = v_frag(dt);
+        const bf16x8 v = v_fragment<D>(vt, lane, dt);
 #pragma unroll
         for (int t = 0; t < NT; ++t)
           oacc[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pb[t], oacc[t][dt], 0, 0, 0);
@@ -490,16 +466,9 @@ __global__ __launch_bounds__(64, D == 64 ? 2 : 1) void cascade_ranges_kernel(Cas
 }
 
 // One work-group per (sequence, KV head): combines the pieces of its group's
-// shared prefix and of its own keys.  A thread holds four features of one row;
-// as many teams of threads as fit and have work share the pieces, each taking kMergeStep
-// at a time with their loads in flight together, and meet in LDS.  (Steps of 8
-// with the last piece read again past the end: 9.4 us where this takes 6.5.)
-constexpr int kMergeStep = 4;
-constexpr int kMergeThreads = 512;     // kMaxGroup * 128 / 4
+// shared prefix and of its own keys.
 template <int D>
 __global__ __launch_bounds__(kMergeThreads) void cascade_ranges_merge_kernel(CascadeParams p) {
-  __shared__ f32x4 team_acc[kMergeThreads];
-  __shared__ float2 team_md[kMergeThreads];
   const int g = blockIdx.x % p.num_kv_heads;
   const int r = blockIdx.x / p.num_kv_heads;
   const ScalarInts plan = (ScalarInts)p.plan;
@@ -509,72 +478,32 @@ __global__ __launch_bounds__(kMergeThreads) void cascade_ranges_merge_kernel(Cas
   const int own_first = rec[4], own_units = rec[5];
   const int w_own = own_first / per;
   const int n_own = own_units > 0 ? (own_first + own_units - 1) / per - w_own + 1 : 0;
-  const float c = p.scale_log2;
-  const int elems = p.group * (D / 4);   // threads of a team
-  const int team = threadIdx.x / elems;
-  const int idx = threadIdx.x - team * elems;
-  const int hj = idx / (D / 4);
-  const int d = idx % (D / 4) * 4;
-  // the row's column block of the shared prefix, its pieces there
-  const int rho = index * p.group + hj;
-  const int cb = rho / p.width;
-  const int cb_first = group_first + cb * n_units;
-  const int w_cb = cb_first / per;
-  const int n_shared = n_units > 0 ? (cb_first + n_units - 1) / per - w_cb + 1 : 0;
-  const int shared_row = (group_cb + cb + w_cb) * p.width + rho % p.width;
-  const int own_row = own_at + (r + w_own - own_w) * p.group + hj;
-  const int n = n_shared + n_own;
-  const int teams = min(kMergeThreads / elems, max(1, ceil_div(n, kMergeStep)));
-  float mx = -INFINITY, den = 0.f;
-  f32x4 acc = f32x4{};
-  if (team < teams) {
-    for (int i = team; i < n; i += kMergeStep * teams) {
-      float2 ml[kMergeStep];
-      f32x4 o[kMergeStep];
+  // row hj's column block of the shared prefix, its pieces there
+  const size_t row = (size_t)r * p.num_q_heads + g * p.group;
+  const int own_row = own_at + (r + w_own - own_w) * p.group;
+  int n_shared = 0, shared_row = 0;
+  auto pieces = [&](int hj) {
+    const int rho = index * p.group + hj;
+    const int cb = rho / p.width;
+    const int cb_first = group_first + cb * n_units;
+    const int w_cb = cb_first / per;
+    n_shared = n_units > 0 ? (cb_first + n_units - 1) / per - w_cb + 1 : 0;
+    shared_row = (group_cb + cb + w_cb) * p.width + rho % p.width;
+    return n_shared + n_own;
+  };
+  merge_pieces<D>(
+      p.ws_o, p.ws_ml, p.group, p.scale_log2, pieces,
+      [&](int hj, int k) {
+        return (size_t)g * p.rows +
+               (k < n_shared ? shared_row + k * p.width : own_row + hj + (k - n_shared) * p.group);
+      },
+      [&](int hj, int d, bf16x4 o) {
 #pragma unroll
-      for (int x = 0; x < kMergeStep; ++x) {
-        const int k = i + x * teams;
-        ml[x] = make_float2(-INFINITY, 0.f);
-        o[x] = f32x4{};
-        if (k >= n) continue;
-        const size_t at = (size_t)g * p.rows +
-                          (k < n_shared ? shared_row + k * p.width : own_row + (k - n_shared) * p.group);
-        ml[x] = *reinterpret_cast<const float2*>(p.ws_ml + 2 * at);
-        o[x] = *reinterpret_cast<const f32x4*>(p.ws_o + at * D + d);
-      }
-      float m_new = mx;
-#pragma unroll
-      for (int x = 0; x < kMergeStep; ++x) m_new = fmaxf(m_new, ml[x].x);
-      const float alpha = __builtin_amdgcn_exp2f((mx - m_new) * c);
-      mx = m_new;
-      acc *= alpha;
-      den *= alpha;
-#pragma unroll
-      for (int x = 0; x < kMergeStep; ++x) {
-        const float wt = __builtin_amdgcn_exp2f((ml[x].x - mx) * c);      // 0 past the last piece
-        acc += wt * o[x];
-        den += wt * ml[x].y;
-      }
-    }
-  }
-  team_acc[threadIdx.x] = acc;
-  team_md[threadIdx.x] = make_float2(mx, den);
-  __syncthreads();
-  if (team != 0) return;
-  float m_all = mx;
-  for (int t = 1; t < teams; ++t) m_all = fmaxf(m_all, team_md[t * elems + idx].x);
-  const float w_first = __builtin_amdgcn_exp2f((mx - m_all) * c);
-  acc *= w_first;
-  den *= w_first;
-  for (int t = 1; t < teams; ++t) {
-    const float2 md = team_md[t * elems + idx];
-    const float wt = __builtin_amdgcn_exp2f((md.x - m_all) * c);      // 0 for a team without pieces
-    acc += wt * team_acc[t * elems + idx];
-    den += wt * md.y;
-  }
-  const size_t row = (size_t)r * p.num_q_heads + g * p.group + hj;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) p.out[row * D + d + e] = __builtin_bit_cast(uint16_t, (__bf16)(acc[e] / den));
+        for (int e = 0; e < 4; ++e) {
+          const __bf16 x = o[e];
+          p.out[(row + hj) * D + d + e] = __builtin_bit_cast(uint16_t, x);
+        }
+      });
 }
 
 }  // namespace

@@ -99,9 +99,7 @@ __device__ __forceinline__ int shared_len_of(const DecParams& p, int r) {
 
 template <int D, int W>
 struct DecLds {
-  // V tile of one wave: 32 keys x D, rows padded by 32 B so that the 32 lanes
-  // of a transposing read (8 keys x 32 B) fall on distinct banks.
-  static constexpr int vStride = D + 16;
+  static constexpr int vStride = v_tile_stride(D);
   union {
     uint16_t v[W][kChunk * vStride];
     struct {
@@ -223,21 +221,7 @@ __global__ __launch_bounds__(64 * (kCascade ? kCascadeWaves : kDecodeWaves)) voi
     }
   };
 
-  // V^T fragment (16 dims x 32 keys) for output tile dt: the slot s of lane
-  // group qd is key 16*(s/4) + 4*qd + s%4, matching the S^T accumulator
-  // layout (tile s/4, register s%4).  ds_read_b64_tr_b16 hands lane j of a
-  // 16-lane group M[4e + j/4][j%4] of the 8-byte rows its lanes address; lane
-  // 16*qd + i addresses key 4*qd + i/4, dims 16*dt + 4*(i%4).
   const uint16_t* vt = sm.v[wave];
-  const int tr_off = (4 * qd + (j >> 2)) * vStride + 4 * (j & 3);
-  auto v_frag = [&](int dt) -> bf16x8 {
-    const uint16_t* base = vt + tr_off + 16 * dt;
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base + 16 * vStride));
-    const i16x4 lohi[2] = {lo, hi};
-    return __builtin_bit_cast(bf16x8, lohi);
-  };
-
   f32x4 oacc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) oacc[dt] = f32x4{};
@@ -307,7 +291,7 @@ __global__ __launch_bounds__(64 * (kCascade ? kCascadeWaves : kDecodeWaves)) voi
     // O^T += V^T P^T
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v_frag(dt), pb, oacc[dt], 0, 0, 0);
+      oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v_fragment<D>(vt, lane, dt), pb, oacc[dt], 0, 0, 0);
   }
 
   // ---- merge the waves' partial softmaxes -----------------------------
@@ -468,11 +452,10 @@ struct RangeCursor {
 
 template <int D>
 __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
-  constexpr int vStride = DecLds<D, 1>::vStride;
+  constexpr int vStride = v_tile_stride(D);
   constexpr int DC = D / 32;
   constexpr int DT = D / 16;
-  constexpr int kRowChunks = D / 8;
-  constexpr int kVLoads = kChunk * kRowChunks / 64;
+  constexpr int kVLoads = kChunk * D / 8 / 64;
   constexpr int kManyUnits = 0xffff;
   __shared__ union {
     struct {
@@ -651,15 +634,6 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
     id0 = bt[b0];
     id1 = bt[min(b0 + 1, (cu.len - 1) / kBlock)];
   };
-  // V^T fragment (16 dims x 32 keys), as in paged_decode_attn_kernel
-  const int tr_off = (4 * qd + (j >> 2)) * vStride + 4 * (j & 3);
-  auto v_frag = [&](int dt) -> bf16x8 {
-    const uint16_t* base = sm.v + tr_off + 16 * dt;
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(base + 16 * vStride));
-    const i16x4 lohi[2] = {lo, hi};
-    return __builtin_bit_cast(bf16x8, lohi);
-  };
   bf16x8 qreg[DC];
   auto load_q = [&](int r) {
 #pragma unroll
@@ -694,21 +668,7 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
 
     for (;;) {
       const int key0 = cur.x * kUnitKeys;
-  #pragma unroll
-      for (int v = 0; v < kVLoads; ++v) {
-        const int cc = lane + 64 * v;
-        *reinterpret_cast<bf16x8*>(&sm.v[(cc / kRowChunks) * vStride + (cc % kRowChunks) * 8]) = vreg[v];
-      }
-      // rows past the end of the sequence (inside its last block) hold zeros:
-      // their probabilities are 0, but 0 times a stale NaN or Inf is NaN
-      if (key0 + kChunk > cur.len) {
-  #pragma unroll
-        for (int v = 0; v < kVLoads; ++v) {
-          const int cc = lane + 64 * v;
-          if (key0 + cc / kRowChunks >= cur.len)
-            *reinterpret_cast<bf16x8*>(&sm.v[(cc / kRowChunks) * vStride + (cc % kRowChunks) * 8]) = bf16x8{};
-        }
-      }
+      store_v_tile<D>(vreg, lane, key0, cur.len, sm.v);
       f32x4 s[2] = {f32x4{}, f32x4{}};
   #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
@@ -755,7 +715,7 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
       l_run = __builtin_fmaf(l_run, alpha, l_unit * beta);
   #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
-        const f32x4 o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v_frag(dt), pb, f32x4{}, 0, 0, 0);
+        const f32x4 o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v_fragment<D>(sm.v, lane, dt), pb, f32x4{}, 0, 0, 0);
   #pragma unroll
         for (int e = 0; e < 4; ++e) oacc[dt][e] = __builtin_fmaf(oacc[dt][e], alpha, o[e] * beta);
       }
@@ -796,19 +756,9 @@ __global__ __launch_bounds__(64) void decode_ranges_kernel(DecParams p) {
 
 // One work-group per (sequence, KV head): combines the pieces that
 // decode_ranges_kernel left of a sequence (a sequence of one piece has its
-// output already).  A thread holds four features of one row; as many teams of
-// threads as fit and have work share the pieces, each taking kMergeStep at a
-// time so that their loads are in flight together, and the teams' results meet
-// in LDS (with all 32 teams that fit, 16 pairs of 560 keys, 8 / 8 heads of 64, 9.4
-// us a call, now 8.5).
-// The launch is one chain of memory latencies (lengths and plan, pieces,
-// output), so what counts is that there are few of them.
-constexpr int kMergeStep = 4;
-constexpr int kMergeThreads = 512;     // kMaxGroup * 128 / 4
+// output already).
 template <int D>
 __global__ __launch_bounds__(kMergeThreads) void decode_ranges_merge_kernel(DecParams p) {
-  __shared__ f32x4 team_acc[kMergeThreads];
-  __shared__ float2 team_md[kMergeThreads];
   const int lane = threadIdx.x & 63;
   const int g = blockIdx.x % p.num_kv_heads;
   const int r = blockIdx.x / p.num_kv_heads;
@@ -835,64 +785,12 @@ __global__ __launch_bounds__(kMergeThreads) void decode_ranges_merge_kernel(DecP
   // from one work-group per pair
   if (units == 0) n = 0;
   if (n == 1) return;
-  const float c = p.scale_log2;
-  const int elems = p.group * (D / 4);   // threads of a team
-  const int teams = min(kMergeThreads / elems, max(1, ceil_div(n, kMergeStep)));
-  const int team = threadIdx.x / elems;
-  const int idx = threadIdx.x - team * elems;
-  const int hj = idx / (D / 4);
-  const int d = idx % (D / 4) * 4;
-  float mx = -INFINITY, den = 0.f;
-  f32x4 acc = f32x4{};
-  if (team < teams) {
-    const size_t base = ((size_t)g * p.slots + first) * p.group + hj;
-    for (int i = team; i < n; i += kMergeStep * teams) {
-      float2 ml[kMergeStep];
-      f32x4 o[kMergeStep];
-#pragma unroll
-      for (int x = 0; x < kMergeStep; ++x) {
-        ml[x] = make_float2(-INFINITY, 0.f);
-        o[x] = f32x4{};
-        if (i + x * teams >= n) continue;
-        const size_t at = base + (size_t)(i + x * teams) * p.group;
-        ml[x] = *reinterpret_cast<const float2*>(p.ws_ml + 2 * at);
-        o[x] = *reinterpret_cast<const f32x4*>(p.ws_o + at * D + d);
-      }
-      float m_new = mx;
-#pragma unroll
-      for (int x = 0; x < kMergeStep; ++x) m_new = fmaxf(m_new, ml[x].x);
-      const float alpha = __builtin_amdgcn_exp2f((mx - m_new) * c);
-      mx = m_new;
-      acc *= alpha;
-      den *= alpha;
-#pragma unroll
-      for (int x = 0; x < kMergeStep; ++x) {
-        const float wt = __builtin_amdgcn_exp2f((ml[x].x - mx) * c);      // 0 past the last piece
-        acc += wt * o[x];
-        den += wt * ml[x].y;
-      }
-    }
-  }
-  team_acc[threadIdx.x] = acc;
-  team_md[threadIdx.x] = make_float2(mx, den);
-  __syncthreads();
-  if (team != 0) return;
-  float m_all = mx;
-  for (int t = 1; t < teams; ++t) m_all = fmaxf(m_all, team_md[t * elems + idx].x);
-  const float w_own = __builtin_amdgcn_exp2f((mx - m_all) * c);
-  acc *= w_own;
-  den *= w_own;
-  for (int t = 1; t < teams; ++t) {
-    const float2 md = team_md[t * elems + idx];
-    const float wt = __builtin_amdgcn_exp2f((md.x - m_all) * c);      // 0 for a team without pieces
-    acc += wt * team_acc[t * elems + idx];
-    den += wt * md.y;
-  }
-  const size_t row = (size_t)r * p.num_q_heads + g * p.group + hj;
-  bf16x4 o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[e] / den);
-  *reinterpret_cast<uint2*>(p.out + row * D + d) = __builtin_bit_cast(uint2, o);
+  const size_t base = ((size_t)g * p.slots + first) * p.group;
+  const size_t row = (size_t)r * p.num_q_heads + g * p.group;
+  merge_pieces<D>(
+      p.ws_o, p.ws_ml, p.group, p.scale_log2, [&](int) { return n; },
+      [&](int hj, int k) { return base + (size_t)k * p.group + hj; },
+      [&](int hj, int d, bf16x4 o) { *reinterpret_cast<uint2*>(p.out + (row + hj) * D + d) = __builtin_bit_cast(uint2, o); });
 }
 
 // One work-group per (sequence, KV head): the final output of cascade decode
